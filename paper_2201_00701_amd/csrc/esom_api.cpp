@@ -40,8 +40,9 @@ struct esom_ctx {
     // 3-D projection: neighbour lists when the caller asks for none
     int32_t *k3idx = nullptr;
     size_t k3idx_bytes = 0;
-    // graph layout: the other position buffer of the synchronous steps
-    float *lay = nullptr;
+    // graph layout: the other position buffer of the synchronous steps and the
+    // nodes' edge lists
+    void *lay = nullptr;
     size_t lay_bytes = 0;
     // optional per-kernel timing: pending event quadruples (prep, main, exact, end)
     bool timing = false;
@@ -661,7 +662,7 @@ void esom_destroy(esom_ctx *c) {
     dev_free(c, reinterpret_cast<void *&>(c->som_xb), c->som_xb_bytes);
     dev_free(c, reinterpret_cast<void *&>(c->nearest), sizeof(int32_t) * (size_t)c->nearest_cap);
     dev_free(c, reinterpret_cast<void *&>(c->k3idx), c->k3idx_bytes);
-    dev_free(c, reinterpret_cast<void *&>(c->lay), c->lay_bytes);
+    dev_free(c, c->lay, c->lay_bytes);
     dev_free(c, reinterpret_cast<void *&>(c->counters), sizeof(unsigned long long) * C_COUNT);
     if (c->sc.join) (void)hipEventDestroy(c->sc.join);
     if (c->sc.fork) (void)hipEventDestroy(c->sc.fork);
@@ -1025,30 +1026,28 @@ int esom_graph_layout(esom_ctx *c, const float *L_hd, int32_t g, int32_t d, cons
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const size_t need = sizeof(float) * 2 * (size_t)g;
+    // without room for the edge lists in the context's budget, the steps search
+    // the neighbour lists themselves
+    int edges = 1;
+    size_t need = layout_workspace_bytes(g, edges);
+    if (need > c->lay_bytes && c->budget && c->held - c->lay_bytes + need > c->budget) {
+        edges = 0;
+        need = layout_workspace_bytes(g, edges);
+    }
     if (need > c->lay_bytes) {
         if (c->lay) {
             e = hipStreamSynchronize(s);
             if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-            dev_free(c, reinterpret_cast<void *&>(c->lay), c->lay_bytes);
+            dev_free(c, c->lay, c->lay_bytes);
             c->lay_bytes = 0;
         }
-        int st = dev_alloc(c, reinterpret_cast<void **>(&c->lay), need);
+        int st = dev_alloc(c, &c->lay, need);
         if (st != ESOM_OK) return st;
         c->lay_bytes = need;
     }
-    // synchronous steps alternate between L_2d and the context's buffer; an
-    // odd count ends in the buffer and is copied back
-    float *bufs[2] = {L_2d, c->lay};
-    for (int t = 0; t < steps; ++t) {
-        e = launch_layout_step(L_hd, g, d, nbr, kg, bufs[t & 1], bufs[(t + 1) & 1], fixed, lp->scale,
-                               lp->repulsion, lp->softening, lp->step, lp->max_move, s);
-        if (e != hipSuccess) return hip_fail(e, "layout step launch");
-    }
-    if (steps & 1) {
-        e = hipMemcpyAsync(L_2d, c->lay, need, hipMemcpyDeviceToDevice, s);
-        if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
-    }
+    e = launch_layout(L_hd, g, d, nbr, kg, L_2d, c->lay, edges, fixed, steps, lp->scale, lp->repulsion,
+                      lp->softening, lp->step, lp->max_move, s);
+    if (e != hipSuccess) return hip_fail(e, "layout launch");
     return ESOM_OK;
 }
 

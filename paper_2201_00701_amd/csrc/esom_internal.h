@@ -224,9 +224,17 @@ hipError_t launch_ablation_project(int algo, const AbProjArgs &p, int num_cus, h
 constexpr int GRAPH_MAX_K = 32;  // neighbours per landmark in the landmark graph
 hipError_t launch_landmark_graph(const float *L, int g, int d, int kg, int32_t *nbr, float *dist2,
                                  hipStream_t s);
-hipError_t launch_layout_step(const float *L, int g, int d, const int32_t *nbr, int kg, const float *lin,
-                              float *lout, const uint8_t *fixed, double scale, double repulsion,
-                              double soft, double step, double max_move, hipStream_t s);
+// One edge of a node in the layout: its partner and |L_u - L_v|.
+struct LayoutEdge {
+    double rest;
+    int v;
+};
+// Bytes of a layout call's workspace, with (edges = 1) or without the nodes'
+// edge lists.
+size_t layout_workspace_bytes(int g, int edges);
+hipError_t launch_layout(const float *L, int g, int d, const int32_t *nbr, int kg, float *l2d, void *ws, int edges,
+                         const uint8_t *fixed, int steps, double scale, double repulsion, double soft, double step,
+                         double max_move, hipStream_t s);
 hipError_t launch_duplicate(float *L, float *l2d, int g, int d, int j, float dx, float dy, hipStream_t s);
 hipError_t launch_remove(float *L, float *l2d, int g, int d, int j, hipStream_t s);
 

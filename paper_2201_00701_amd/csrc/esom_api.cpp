@@ -743,8 +743,8 @@ int grow_nearest(esom_ctx *c, int64_t n, hipStream_t s) {
     return st;
 }
 
-int grow_update_ws(esom_ctx *c, int64_t n, int g, int d, hipStream_t s) {
-    const size_t need = update_workspace_bytes(n, g, d);
+int grow_update_ws(esom_ctx *c, int64_t n, int g, int d, int64_t nearest_ld, hipStream_t s) {
+    const size_t need = update_workspace_bytes(n, g, d, nearest_ld, c->budget != 0);
     if (need <= c->uws_bytes) return ESOM_OK;
     if (c->uws) {
         hipError_t e = hipStreamSynchronize(s);
@@ -782,6 +782,15 @@ int esom_som_train(esom_ctx *c, const float *X, int64_t n, int32_t d, int64_t ld
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (som_direct(batch, g, d)) {
+        if ((st = grow_nearest(c, batch, s)) != ESOM_OK) return st;
+        for (int t = 0; t < steps; ++t) {
+            e = launch_som_direct(X, n, ldx, d, L_hd, L_2d, g, batch_idx + (size_t)t * batch, batch, c->nearest,
+                                  sigma[t], alpha[t], frozen, s);
+            if (e != hipSuccess) return hip_fail(e, "online SOM step launch");
+        }
+        return ESOM_OK;
+    }
     const size_t xb = sizeof(float) * (size_t)batch * d;
     if (xb > c->som_xb_bytes) {
         if (c->som_xb) {
@@ -795,7 +804,7 @@ int esom_som_train(esom_ctx *c, const float *X, int64_t n, int32_t d, int64_t ld
         c->som_xb_bytes = xb;
     }
     if ((st = grow_nearest(c, batch, s)) != ESOM_OK) return st;
-    if ((st = grow_update_ws(c, batch, g, d, s)) != ESOM_OK) return st;
+    if ((st = grow_update_ws(c, batch, g, d, 1, s)) != ESOM_OK) return st;
     esom_params P;
     esom_default_params(&P);
     P.k = 1;
@@ -826,7 +835,7 @@ int esom_som_train(esom_ctx *c, const float *X, int64_t n, int32_t d, int64_t ld
         u.counts = nullptr;
         u.frozen = frozen;
         u.batch = batch;
-        e = launch_update(u, c->uws, c->num_cus, s);
+        e = launch_update(u, c->uws, c->budget != 0, s);
         if (e != hipSuccess) return hip_fail(e, "online SOM update launch");
     }
     return ESOM_OK;
@@ -893,18 +902,8 @@ int esom_landmark_update(esom_ctx *c, const float *X, int64_t n, int32_t d, int6
         if (st != ESOM_OK) return st;
         near = c->nearest;
     }
-    const size_t need = update_workspace_bytes(n, g, d);
-    if (need > c->uws_bytes) {
-        if (c->uws) {
-            e = hipStreamSynchronize(s);
-            if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-            dev_free(c, c->uws, c->uws_bytes);
-            c->uws_bytes = 0;
-        }
-        st = dev_alloc(c, &c->uws, need);
-        if (st != ESOM_OK) return st;
-        c->uws_bytes = need;
-    }
+    st = grow_update_ws(c, n, g, d, near_ld, s);
+    if (st != ESOM_OK) return st;
     UpdateArgs u;
     u.X = X;
     u.n = n;
@@ -919,7 +918,7 @@ int esom_landmark_update(esom_ctx *c, const float *X, int64_t n, int32_t d, int6
     u.nearest = near;
     u.nearest_ld = near_ld;
     u.counts = counts;
-    e = launch_update(u, c->uws, c->num_cus, s);
+    e = launch_update(u, c->uws, c->budget != 0, s);
     if (e != hipSuccess) return hip_fail(e, "landmark update launch");
     return ESOM_OK;
 }

@@ -169,8 +169,11 @@ struct UpdateArgs {
     const uint8_t *frozen = nullptr;  // kind 2: landmarks that keep their position
     int64_t batch = 1;                // kind 2: batch size of the averaged online step
 };
-size_t update_workspace_bytes(int64_t n, int g, int d);
-hipError_t launch_update(const UpdateArgs &u, void *ws, int num_cus, hipStream_t s);
+// Workspace of an update of n points whose nearest landmarks lie nearest_ld
+// apart; tight (contexts with a memory budget): the sums and at most 4 bytes a
+// point.  launch_update takes the same `tight`.
+size_t update_workspace_bytes(int64_t n, int g, int d, int64_t nearest_ld, bool tight);
+hipError_t launch_update(const UpdateArgs &u, void *ws, bool tight, hipStream_t s);
 
 // The materialised-distance path (esom_materialise.hip): keys of a chunk of
 // points in device memory, then selection, exact rescoring and certificate.
@@ -242,6 +245,12 @@ hipError_t launch_remove(float *L, float *l2d, int g, int d, int j, hipStream_t 
 hipError_t launch_som_gather(const float *X, int64_t n, int64_t ldx, int d, const int32_t *rows, int B,
                              float *Xb, hipStream_t s);
 hipError_t launch_som_mask(const int32_t *rows, int B, int64_t n, int32_t *nearest, hipStream_t s);
+// One online step on a batch small enough for the direct path (som_direct):
+// nearest landmarks into `nearest` (B entries), then the update of L.
+bool som_direct(int B, int g, int d);
+hipError_t launch_som_direct(const float *X, int64_t n, int64_t ldx, int d, float *L, const float *l2d, int g,
+                             const int32_t *rows, int B, int32_t *nearest, float sigma, float alpha,
+                             const uint8_t *frozen, hipStream_t s);
 hipError_t launch_fit_landmarks(const float *L, const float *l2d, int g, int d, const float *p, int m,
                                 int kfit, float sigma, float *out, hipStream_t s);
 

@@ -2,11 +2,9 @@
 // batch-SOM blend (semi-supervised model update of the paper's supervision
 // section, in data-parallel batch form).
 //
-// Points are bucketed by nearest landmark with a counting sort (per-block
-// LDS histograms, one global scan, per-block range claims), then every
-// bucket's rows are summed in FP64 in chunks with coalesced row reads.  FP64
-// sums make the result independent of the visiting order up to FP64
-// rounding, far below the FP32 output rounding.
+// The rows stream once into FP64 sums kept in LDS (upd_accum), and the blocks'
+// sums are added (upd_reduce).  FP64 sums make the result independent of the
+// visiting order up to FP64 rounding, far below the FP32 output rounding.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -16,192 +14,211 @@
 namespace esom {
 
 constexpr int UPD_BLOCK = 256;
-constexpr int UPD_CHUNK = 4096;  // points per histogram block / per summing chunk
-constexpr int UPD_SCAN = 1024;   // threads of the scan block
 
-// counts[j] += number of points whose nearest landmark is j.
-__global__ void upd_hist(const int32_t *__restrict__ nearest, int64_t ld, int64_t n, int g,
-                         int *__restrict__ counts) {
-    extern __shared__ int hist[];
-    for (int j = threadIdx.x; j < g; j += blockDim.x) hist[j] = 0;
-    __syncthreads();
-    const int64_t b0 = (int64_t)blockIdx.x * UPD_CHUNK;
-    const int64_t b1 = b0 + UPD_CHUNK < n ? b0 + UPD_CHUNK : n;
-    for (int64_t i = b0 + threadIdx.x; i < b1; i += blockDim.x) {
-        const int j = nearest[i * ld];
-        if (j >= 0 && j < g) atomicAdd(&hist[j], 1);  // invalid indices are ignored
-    }
-    __syncthreads();
-    for (int j = threadIdx.x; j < g; j += blockDim.x)
-        if (hist[j]) atomicAdd(&counts[j], hist[j]);
+// Sums of the rows by nearest landmark in LDS.  The landmarks go in groups whose
+// gg x d FP64 sums fit in LDS, the points in P ranges; a block takes one group and
+// one range.  Each wavefront takes 64 points at a time, lists those of its group
+// (their order in memory, so the blocks of a range read its rows as one stream),
+// and adds the rows with LDS atomics, LP lanes a row (LP >= d up to 64, NQ
+// dimensions a lane beyond), ACC_U loads in flight.  Blocks 8 apart (the same XCD)
+// take the groups of one range.  The partial array of a range is [g][d + 1], the
+// count last.
+// Bound by the LDS atomics, which take an FP64 lane a clock (10M x 64-D: 2.5M
+// adds per CU, 1.0 ms; the row stream alone takes 0.55).  10M x 64-D, 1024
+// landmarks: a counting sort of all points and one block per 4096 points of a
+// landmark took 2.41 ms (sums 1.94, scatter 0.33, histogram 0.13); ranges sorted
+// in LDS and summed in registers 1.70 ms (rows gathered in random order, 1.9
+// TB/s); this 1.75 ms with upd_compact, and for every landmark count.  1M x 32-D,
+// 400 landmarks: 0.36 ms by the sort, now 0.063 ms.
+constexpr int ACC_BLOCK = 1024;
+constexpr int ACC_U = 16;                           // row loads in flight per LP lanes (divided by NQ)
+constexpr int ACC_RANGE = 1024;                     // points per range at least
+constexpr int ACC_BLOCKS = 256;                     // blocks at most (one per CU)
+constexpr size_t ACC_LDS_BYTES = (size_t)148 << 10;  // sums and counts of a group
+
+__device__ __forceinline__ void lds_add_f64(double *p, double v) {
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Exclusive scans of the counts (offsets[0..g], cursors) and of the chunks per
-// landmark (ceil(count / UPD_CHUNK)), then the chunk table: chunk c covers
-// [chunk_start, +UPD_CHUNK) of landmark chunk_landmark's range, landmark by
-// landmark.  One block; each thread owns a contiguous run of landmarks.
-__global__ void __launch_bounds__(UPD_SCAN) upd_scan(const int *__restrict__ counts, int g,
-                                                     int64_t *__restrict__ offsets,
-                                                     unsigned long long *__restrict__ cursor,
-                                                     int *__restrict__ chunk_landmark,
-                                                     int *__restrict__ chunk_start, int *__restrict__ nchunks) {
-    __shared__ long long sp[UPD_SCAN];
-    __shared__ int sc[UPD_SCAN];
-    const int per = (g + UPD_SCAN - 1) / UPD_SCAN;
-    const int j0 = threadIdx.x * per, j1 = j0 + per < g ? j0 + per : g;
-    long long pts = 0;
-    int chk = 0;
-    for (int j = j0; j < j1; ++j) {
-        pts += counts[j];
-        chk += (counts[j] + UPD_CHUNK - 1) / UPD_CHUNK;
-    }
-    sp[threadIdx.x] = pts;
-    sc[threadIdx.x] = chk;
+template <int LP, int NQ>
+__global__ void __launch_bounds__(ACC_BLOCK) upd_accum(const float *__restrict__ X, int64_t n, int64_t ldx, int d,
+                                                       const int32_t *__restrict__ nearest, int64_t ld, int g,
+                                                       int gg, int groups, int P, double *__restrict__ partial) {
+    extern __shared__ __align__(16) unsigned char asm_[];
+    __shared__ int2 lists[ACC_BLOCK / 64][64];
+    const int grp = (blockIdx.x / 8) % groups, rng = (blockIdx.x / (8 * groups)) * 8 + blockIdx.x % 8;
+    if (rng >= P) return;
+    const int j0 = grp * gg, gn = g - j0 < gg ? g - j0 : gg;  // this group's landmarks
+    double *acc = reinterpret_cast<double *>(asm_);           // gn x d
+    int *cnt = reinterpret_cast<int *>(acc + (size_t)gg * d);
+    const int tid = threadIdx.x, lane64 = tid & 63, wv = tid >> 6, lane = lane64 % LP, sub = lane64 / LP;
+    for (int e = tid; e < gn * d; e += ACC_BLOCK) acc[e] = 0.0;
+    for (int e = tid; e < gn; e += ACC_BLOCK) cnt[e] = 0;
     __syncthreads();
-    // inclusive Hillis-Steele scans of the per-thread totals
-    for (int o = 1; o < UPD_SCAN; o <<= 1) {
-        const long long a = threadIdx.x >= o ? sp[threadIdx.x - o] : 0;
-        const int b = threadIdx.x >= o ? sc[threadIdx.x - o] : 0;
-        __syncthreads();
-        sp[threadIdx.x] += a;
-        sc[threadIdx.x] += b;
-        __syncthreads();
-    }
-    long long run = sp[threadIdx.x] - pts;
-    int c = sc[threadIdx.x] - chk;
-    for (int j = j0; j < j1; ++j) {
-        offsets[j] = run;
-        cursor[j] = (unsigned long long)run;
-        run += counts[j];
-        for (int s0 = 0; s0 < counts[j]; s0 += UPD_CHUNK) {
-            chunk_landmark[c] = j;
-            chunk_start[c] = s0;
-            ++c;
+    constexpr int PP = 64 / LP, U = ACC_U / NQ;
+    int2 *list = lists[wv];
+    const int64_t per = ((n + P - 1) / P + 63) & ~(int64_t)63;
+    const int64_t r0 = rng * per, r1 = r0 + per < n ? r0 + per : n;
+    int64_t i = r0 + 64 * wv + lane64;
+    int jn = i < r1 ? nearest[i * ld] : -1;
+    for (int64_t ib = r0 + 64 * wv; ib < r1; ib += ACC_BLOCK) {
+        const int j = jn - j0;
+        const bool in = jn >= 0 && jn < g && j >= 0 && j < gn;  // indices outside [0, g) are ignored
+        const unsigned long long mk = __ballot(in);
+        const int m = __popcll(mk);
+        if (in) {
+            list[__popcll(mk & ((1ull << lane64) - 1ull))] = make_int2((int)(i - r0), j);
+            atomicAdd(&cnt[j], 1);
         }
-    }
-    if (threadIdx.x == UPD_SCAN - 1) {
-        offsets[g] = sp[UPD_SCAN - 1];
-        *nchunks = sc[UPD_SCAN - 1];
-    }
-}
-
-// Scatter point indices into their landmark's range.
-__global__ void upd_scatter(const int32_t *__restrict__ nearest, int64_t ld, int64_t n, int g,
-                            unsigned long long *__restrict__ cursor, int32_t *__restrict__ perm) {
-    extern __shared__ int sh[];
-    int *hist = sh;                                               // g: block histogram
-    int *base = sh + g;                                           // g: next slot in the claim
-    long long *claim = reinterpret_cast<long long *>(sh + 2 * g);  // g: this block's range start
-    for (int j = threadIdx.x; j < g; j += blockDim.x) hist[j] = 0;
-    __syncthreads();
-    const int64_t b0 = (int64_t)blockIdx.x * UPD_CHUNK;
-    const int64_t b1 = b0 + UPD_CHUNK < n ? b0 + UPD_CHUNK : n;
-    for (int64_t i = b0 + threadIdx.x; i < b1; i += blockDim.x) {
-        const int j = nearest[i * ld];
-        if (j >= 0 && j < g) atomicAdd(&hist[j], 1);
-    }
-    __syncthreads();
-    for (int j = threadIdx.x; j < g; j += blockDim.x) {
-        base[j] = 0;
-        claim[j] = hist[j] ? (long long)atomicAdd(&cursor[j], (unsigned long long)hist[j]) : 0;
-    }
-    __syncthreads();
-    for (int64_t i = b0 + threadIdx.x; i < b1; i += blockDim.x) {
-        const int j = nearest[i * ld];
-        if (j < 0 || j >= g) continue;
-        const int pos = atomicAdd(&base[j], 1);
-        perm[claim[j] + pos] = (int32_t)i;
-    }
-}
-
-// FP64 sums of the rows in one chunk of one landmark's range.  Block = one
-// chunk; threads stride over dimensions (rows are read contiguously).
-__global__ void upd_sum(const float *__restrict__ X, int64_t ldx, int d,
-                        const int32_t *__restrict__ perm, const int64_t *__restrict__ offsets,
-                        const int *__restrict__ chunk_landmark, const int *__restrict__ chunk_start,
-                        const int *__restrict__ nchunks, double *__restrict__ sums) {
-    const int c = blockIdx.x;
-    if (c >= *nchunks) return;
-    const int j = chunk_landmark[c];
-    const int64_t beg = offsets[j] + (int64_t)chunk_start[c];
-    int64_t end = beg + UPD_CHUNK;
-    if (end > offsets[j + 1]) end = offsets[j + 1];
-    // Several rows per pass: the block is split into groups of `tpr` threads per row.
-    const int tpr = d <= 32 ? 32 : 64;
-    const int rows_per_pass = blockDim.x / tpr;
-    const int sub = threadIdx.x / tpr, t0 = threadIdx.x % tpr;
-    __shared__ double red[UPD_BLOCK / 32][ESOM_MAX_D];
-    double acc[ESOM_MAX_D / 32];
+        i += ACC_BLOCK;
+        jn = i < r1 ? nearest[i * ld] : -1;  // the next 64 points' landmarks
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (int p0 = 0; p0 < m; p0 += U * PP) {
+            int jj[U];
+            float x[U][NQ];
 #pragma unroll
-    for (int q = 0; q < ESOM_MAX_D / 32; ++q) acc[q] = 0.0;
-    for (int64_t r = beg + sub; r < end; r += rows_per_pass) {
-        const float *xr = X + (int64_t)perm[r] * ldx;
+            for (int u = 0; u < U; ++u) {
+                const int at = p0 + u * PP + sub;
+                const int2 pt = list[at < m ? at : 0];
+                jj[u] = at < m ? pt.y : -1;
+                const float *xr = X + (r0 + pt.x) * ldx;
 #pragma unroll
-        for (int q = 0; q < ESOM_MAX_D / 32; ++q) {
-            const int t = t0 + q * tpr;
-            if (t < d) acc[q] += (double)xr[t];
+                for (int q = 0; q < NQ; ++q) x[u][q] = at < m && lane + LP * q < d ? xr[lane + LP * q] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int q = 0; q < NQ; ++q)
+                    if (jj[u] >= 0 && lane + LP * q < d) lds_add_f64(&acc[jj[u] * d + lane + LP * q], (double)x[u][q]);
         }
-    }
-#pragma unroll
-    for (int q = 0; q < ESOM_MAX_D / 32; ++q) {
-        const int t = t0 + q * tpr;
-        if (t < d) red[sub][t] = acc[q];
+        __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < d; t += blockDim.x) {
-        double s = 0.0;
-        for (int q = 0; q < rows_per_pass; ++q) s += red[q][t];
-        atomicAdd(&sums[(size_t)j * (d + 1) + t], s);
+    double *out = partial + ((size_t)rng * g + j0) * (d + 1);
+    for (int j = tid / LP; j < gn; j += ACC_BLOCK / LP) {
+        for (int t = lane; t < d; t += LP) out[(size_t)j * (d + 1) + t] = acc[j * d + t];
+        if (lane == 0) out[(size_t)j * (d + 1) + d] = (double)cnt[j];
     }
-    if (threadIdx.x == 0) atomicAdd(&sums[(size_t)j * (d + 1) + d], (double)(end - beg));
 }
 
-// Blend: one block per landmark j, threads over dimensions.  kind 0: k-means;
-// kind 1: batch SOM; kind 2: one online SOM step over a batch of `batch`
-// points, the average of the single-point online updates
-//   L_j += (alpha / batch) sum_b h_jb (S_b - c_b L_j),
-// skipping landmarks with frozen[j] != 0.
-__global__ void upd_finalize(const double *__restrict__ sums, const float *__restrict__ l2d, int g,
-                             int d, int kind, float alpha, float sigma, float *__restrict__ L,
-                             const int *__restrict__ counts, int32_t *__restrict__ counts_out,
-                             const uint8_t *__restrict__ frozen, int64_t batch) {
+// near[i] = nearest[i * ld]: every group would read a strided list's lines again.
+__global__ void upd_compact(const int32_t *__restrict__ nearest, int64_t ld, int64_t n, int32_t *__restrict__ near) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) near[i] = nearest[i * ld];
+}
+
+// Adds the P partial sums of landmark j = blockIdx.x, the threads sharing the
+// partials of each of the d + 1 columns; then the k-means blend (kind 0) or the
+// sums for the topology blend (S).
+__global__ void __launch_bounds__(UPD_BLOCK) upd_reduce(const double *partial, int P, int g, int d, int kind,
+                                                        float alpha, float *__restrict__ L, double *S,
+                                                        int32_t *__restrict__ counts_out) {
+    __shared__ double red[UPD_BLOCK + ESOM_MAX_D + 1];  // share x column
     const int j = blockIdx.x;
-    if (j >= g) return;
-    if (counts_out && threadIdx.x == 0) counts_out[j] = counts[j];
-    if (kind == 2 && frozen && frozen[j]) return;
-    double den = 0.0;
-    const double s2 = 2.0 * (double)sigma * (double)sigma;
-    if (kind == 0) {
-        den = sums[(size_t)j * (d + 1) + d];
-    } else {
-        for (int b = 0; b < g; ++b) {
-            double hjb;
-            if (sigma == 0.f) {
-                hjb = b == j ? 1.0 : 0.0;
-            } else {
-                const double dx = (double)l2d[2 * j] - (double)l2d[2 * b];
-                const double dy = (double)l2d[2 * j + 1] - (double)l2d[2 * b + 1];
-                hjb = exp(-(dx * dx + dy * dy) / s2);
-            }
-            den += hjb * sums[(size_t)b * (d + 1) + d];
+    const int cols = d + 1;
+    const int ns = cols < UPD_BLOCK ? UPD_BLOCK / cols : 1;  // shares
+    for (int e = threadIdx.x; e < ns * cols; e += UPD_BLOCK) {
+        const int sh = e / cols, t = e % cols;
+        double s = 0.0;
+#pragma unroll 16
+        for (int p = sh; p < P; p += ns) s += partial[((size_t)p * g + j) * cols + t];
+        red[e] = s;
+    }
+    __syncthreads();
+    auto total = [&](int t) {
+        double s = 0.0;
+        for (int sh = 0; sh < ns; ++sh) s += red[sh * cols + t];
+        return s;
+    };
+    const double den = total(d);
+    if (counts_out && threadIdx.x == 0) counts_out[j] = (int32_t)den;
+    for (int t = threadIdx.x; t < cols; t += blockDim.x) {
+        if (kind != 0) {
+            S[(size_t)j * cols + t] = total(t);
+        } else if (t < d && den > 0.0) {
+            const double Lj = (double)L[(size_t)j * d + t];
+            L[(size_t)j * d + t] = (float)(Lj + (double)alpha * (total(t) / den - Lj));
         }
     }
-    for (int t = threadIdx.x; t < d; t += blockDim.x) {
-        double num = 0.0;
-        if (kind == 0) {
-            num = sums[(size_t)j * (d + 1) + t];
-        } else {
-            for (int b = 0; b < g; ++b) {
-                double hjb;
-                if (sigma == 0.f) {
-                    hjb = b == j ? 1.0 : 0.0;
-                } else {
-                    const double dx = (double)l2d[2 * j] - (double)l2d[2 * b];
-                    const double dy = (double)l2d[2 * j + 1] - (double)l2d[2 * b + 1];
-                    hjb = exp(-(dx * dx + dy * dy) / s2);
-                }
-                num += hjb * sums[(size_t)b * (d + 1) + t];
+}
+
+// Blends over the 2-D topology, L_j from sum_b h_jb (S_b, c_b).  kind 1: batch
+// SOM; kind 2: one online SOM step over a batch of `batch` points, the average
+// of the single-point online updates
+//   L_j += (alpha / batch) sum_b h_jb (S_b - c_b L_j),
+// skipping landmarks with frozen[j] != 0.  A block takes BLEND_J landmarks j and
+// walks the landmarks b in chunks of BLEND_B: its threads form the chunk's
+// BLEND_J x BLEND_B weights in LDS (one exponential each), then each wavefront
+// adds its share of the chunk's rows, lanes over the d + 1 columns of S (the
+// count is the last), and the wavefronts' sums meet in LDS.
+// Bound by the latency of the chunk steps; two landmarks a block keep 200
+// blocks in flight at g = 400.  400 landmarks, 32-D: every thread used to
+// evaluate all g exponentials for itself, twice, 287 us; now 13 us.
+constexpr int BLEND_J = 2;
+constexpr int BLEND_B = UPD_BLOCK / BLEND_J;
+
+template <int NQ>
+__global__ void __launch_bounds__(UPD_BLOCK) upd_blend(const double *__restrict__ sums, const float *__restrict__ l2d,
+                                                       int g, int d, int kind, float alpha, float sigma,
+                                                       float *__restrict__ L, const uint8_t *__restrict__ frozen,
+                                                       int64_t batch) {
+    constexpr int NW = UPD_BLOCK / 64;
+    __shared__ double h[BLEND_J][BLEND_B];
+    __shared__ double red[NW][BLEND_J][64 * NQ];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int j0 = blockIdx.x * BLEND_J;
+    const int cols = d + 1;
+    const double s2 = 2.0 * (double)sigma * (double)sigma;
+    const int hj = threadIdx.x / BLEND_B, hb = threadIdx.x % BLEND_B;
+    const int jh = min(j0 + hj, g - 1);
+    const double jx = (double)l2d[2 * jh], jy = (double)l2d[2 * jh + 1];
+    double acc[BLEND_J][NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int i = 0; i < BLEND_J; ++i) acc[i][q] = 0.0;
+    for (int b0 = 0; b0 < g; b0 += BLEND_B) {
+        __syncthreads();
+        const int bh = b0 + hb;
+        double w = 0.0;
+        if (bh < g) {
+            if (sigma == 0.f) {
+                w = bh == jh ? 1.0 : 0.0;
+            } else {
+                const double dx = jx - (double)l2d[2 * bh], dy = jy - (double)l2d[2 * bh + 1];
+                w = exp(-(dx * dx + dy * dy) / s2);
             }
+        }
+        h[hj][hb] = w;
+        __syncthreads();
+        const int nb = g - b0 < BLEND_B ? g - b0 : BLEND_B;
+#pragma unroll 8
+        for (int b = wv; b < nb; b += NW) {
+            const double *Sb = sums + (size_t)(b0 + b) * cols;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int t = lane + 64 * q;
+                const double v = t < cols ? Sb[t] : 0.0;
+#pragma unroll
+                for (int i = 0; i < BLEND_J; ++i) acc[i][q] = fma(h[i][b], v, acc[i][q]);
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int i = 0; i < BLEND_J; ++i) red[wv][i][lane + 64 * q] = acc[i][q];
+    __syncthreads();
+    for (int e = threadIdx.x; e < BLEND_J * d; e += UPD_BLOCK) {
+        const int i = e / d, t = e % d, j = j0 + i;
+        if (j >= g || (kind == 2 && frozen && frozen[j])) continue;
+        double num = 0.0, den = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            num += red[w][i][t];
+            den += red[w][i][d];
         }
         const double Lj = (double)L[(size_t)j * d + t];
         if (kind == 2)
@@ -211,65 +228,70 @@ __global__ void upd_finalize(const double *__restrict__ sums, const float *__res
     }
 }
 
-__global__ void upd_zero(double *__restrict__ sums, size_t ns, int *__restrict__ counts, int g) {
-    const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < ns) sums[e] = 0.0;
-    if (e < (size_t)g) counts[e] = 0;
+static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// Landmark groups of a shape, and the ranges n points go in: together enough
+// blocks to fill the chip once, each range of at least ACC_RANGE points.  One
+// range needs no partial array beside the sums.  tight (contexts with a memory
+// budget): the partial arrays take no more than 4 bytes a point.
+static int acc_group(int g, int d) {
+    const int gg = (int)(ACC_LDS_BYTES / (sizeof(double) * d + sizeof(int)));
+    const int groups = (g + gg - 1) / gg;
+    return (g + groups - 1) / groups;
+}
+static int acc_groups(int g, int d) { return (g + acc_group(g, d) - 1) / acc_group(g, d); }
+static int acc_ranges(int64_t n, int g, int d, bool tight) {
+    int64_t r = (n + ACC_RANGE - 1) / ACC_RANGE;
+    if (r > ACC_BLOCKS / acc_groups(g, d)) r = ACC_BLOCKS / acc_groups(g, d);
+    if (tight) {
+        const int64_t most = (int64_t)(sizeof(int32_t) * (size_t)n / (sizeof(double) * (size_t)g * (d + 1)));
+        if (r > most) r = most;
+    }
+    return r < 1 ? 1 : (int)r;
+}
+static bool acc_compact(int g, int d, int64_t nearest_ld, bool tight) {
+    return acc_groups(g, d) > 1 && nearest_ld > 1 && !tight;
 }
 
-// Workspace layout (bytes, each region 256-aligned), computed by the caller.
-size_t update_workspace_bytes(int64_t n, int g, int d) {
-    auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    const int64_t maxchunks = n / UPD_CHUNK + g + 1;
-    return al(sizeof(double) * (size_t)g * (d + 1)) + al(sizeof(int) * g) +
-           al(sizeof(int64_t) * (g + 1)) + al(sizeof(unsigned long long) * g) +
-           al(sizeof(int32_t) * (size_t)(n > 0 ? n : 1)) + 2 * al(sizeof(int) * (size_t)maxchunks) +
-           al(sizeof(int));
+size_t update_workspace_bytes(int64_t n, int g, int d, int64_t nearest_ld, bool tight) {
+    const size_t sums = sizeof(double) * (size_t)g * (d + 1);
+    const int r = acc_ranges(n, g, d, tight);
+    return al256(sums) + (r > 1 ? al256(sums * r) : 0) +
+           (acc_compact(g, d, nearest_ld, tight) ? al256(sizeof(int32_t) * (size_t)(n > 0 ? n : 1)) : 0);
 }
 
-hipError_t launch_update(const UpdateArgs &u, void *ws, int num_cus, hipStream_t s) {
-    (void)num_cus;
-    auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
+hipError_t launch_update(const UpdateArgs &u, void *ws, bool tight, hipStream_t s) {
+    const size_t sb = sizeof(double) * (size_t)u.g * (u.d + 1);
     char *p = static_cast<char *>(ws);
-    double *sums = reinterpret_cast<double *>(p);
-    p += al(sizeof(double) * (size_t)u.g * (u.d + 1));
-    int *counts = reinterpret_cast<int *>(p);
-    p += al(sizeof(int) * u.g);
-    int64_t *offsets = reinterpret_cast<int64_t *>(p);
-    p += al(sizeof(int64_t) * (u.g + 1));
-    unsigned long long *cursor = reinterpret_cast<unsigned long long *>(p);
-    p += al(sizeof(unsigned long long) * u.g);
-    int32_t *perm = reinterpret_cast<int32_t *>(p);
-    p += al(sizeof(int32_t) * (size_t)(u.n > 0 ? u.n : 1));
-    const int64_t maxchunks = u.n / UPD_CHUNK + u.g + 1;
-    int *chunk_landmark = reinterpret_cast<int *>(p);
-    p += al(sizeof(int) * (size_t)maxchunks);
-    int *chunk_start = reinterpret_cast<int *>(p);
-    p += al(sizeof(int) * (size_t)maxchunks);
-    int *nchunks = reinterpret_cast<int *>(p);
-
-    const size_t ns = (size_t)u.g * (u.d + 1);
-    const size_t nz = ns > (size_t)u.g ? ns : (size_t)u.g;
-    hipLaunchKernelGGL(upd_zero, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, s, sums, ns,
-                       counts, u.g);
-    const unsigned hblocks = (unsigned)((u.n + UPD_CHUNK - 1) / UPD_CHUNK);
-    if (u.n > 0) {
-        hipLaunchKernelGGL(upd_hist, dim3(hblocks), dim3(UPD_BLOCK), sizeof(int) * u.g, s, u.nearest,
-                           u.nearest_ld, u.n, u.g, counts);
+    double *sums = reinterpret_cast<double *>(p), *partial = sums;
+    p += al256(sb);
+    const int ranges = acc_ranges(u.n, u.g, u.d, tight);
+    if (ranges > 1) {
+        partial = reinterpret_cast<double *>(p);
+        p += al256(sb * ranges);
     }
-    hipLaunchKernelGGL(upd_scan, dim3(1), dim3(UPD_SCAN), 0, s, counts, u.g, offsets, cursor,
-                       chunk_landmark, chunk_start, nchunks);
-    if (u.n > 0) {
-        const size_t sh = sizeof(int) * 2 * (size_t)u.g + sizeof(long long) * (size_t)u.g;
-        hipLaunchKernelGGL(upd_scatter, dim3(hblocks), dim3(UPD_BLOCK), sh, s, u.nearest, u.nearest_ld,
-                           u.n, u.g, cursor, perm);
-        // Grid sized for the worst case; blocks past the chunk count exit at once.
-        hipLaunchKernelGGL(upd_sum, dim3((unsigned)maxchunks), dim3(UPD_BLOCK), 0, s, u.X, u.ldx,
-                           u.d, perm, offsets, chunk_landmark, chunk_start, nchunks, sums);
+    const int32_t *near = u.nearest;
+    int64_t ld = u.nearest_ld;
+    if (u.n > 0 && acc_compact(u.g, u.d, ld, tight)) {
+        int32_t *c = reinterpret_cast<int32_t *>(p);
+        hipLaunchKernelGGL(upd_compact, dim3((unsigned)((u.n + 255) / 256)), dim3(256), 0, s, near, ld, u.n, c);
+        near = c;
+        ld = 1;
     }
-    hipLaunchKernelGGL(upd_finalize, dim3(u.g), dim3(u.d < 256 ? 64 * ((u.d + 63) / 64) : 256), 0, s,
-                       sums, u.l2d, u.g, u.d, u.kind, u.alpha, u.sigma, u.L, counts, u.counts,
-                       u.frozen, u.batch);
+    const int gg = acc_group(u.g, u.d), groups = acc_groups(u.g, u.d);
+    const size_t sh = (sizeof(double) * u.d + sizeof(int)) * (size_t)gg;
+    auto acc = u.d <= 16 ? upd_accum<16, 1> : u.d <= 32 ? upd_accum<32, 1> : u.d <= 64 ? upd_accum<64, 1>
+              : u.d <= 128 ? upd_accum<64, 2> : upd_accum<64, 4>;
+    hipLaunchKernelGGL(acc, dim3((ranges + 7) / 8 * 8 * groups), dim3(ACC_BLOCK), sh, s, u.X, u.n, u.ldx, u.d, near,
+                       ld, u.g, gg, groups, ranges, partial);
+    // (one range: reduced in place for the topology blends)
+    hipLaunchKernelGGL(upd_reduce, dim3(u.g), dim3(UPD_BLOCK), 0, s, partial, ranges, u.g, u.d, u.kind, u.alpha, u.L,
+                       sums, u.counts);
+    if (u.kind != 0) {
+        auto kern = u.d < 64 ? upd_blend<1> : u.d < 128 ? upd_blend<2> : upd_blend<5>;
+        hipLaunchKernelGGL(kern, dim3((u.g + BLEND_J - 1) / BLEND_J), dim3(UPD_BLOCK), 0, s, sums, u.l2d, u.g, u.d,
+                           u.kind, u.alpha, u.sigma, u.L, u.frozen, u.batch);
+    }
     return hipGetLastError();
 }
 

@@ -1043,104 +1043,112 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                 store(tp);
             }
         };
-        // BF16 mode's pass 2 for points in locality order: the high product
-        // first, which is the pass-1 key (same operands, same order, error at
-        // most E16).  A 32-point half whose keys of the tile all exceed its
-        // points' tau + E16 + E2 (pass-2 keys then exceed tau) has no candidate
-        // there: the low products are skipped and the tile's bits marked "not
-        // a candidate".  The points of a wavefront share a neighbourhood, and
-        // most tiles hold no candidate of theirs.
-        auto screen_pass_split_skip = [&](auto in_lds, auto consume, auto store, const float (&thr)[2]) {
-            const void *Ab = decltype(in_lds)::value ? static_cast<const void *>(tilesL) : a.A;
+        // Points in locality order: a wavefront's points share a neighbourhood,
+        // and most tiles hold no candidate of theirs.  Pass 1 then also keeps,
+        // per lane and tile, the smallest approximate delta^2 (key + |x - c|^2)
+        // of both points, rounded down to 16 bits, in the words where pass 2 will
+        // put the tile's candidate bits: the word of (p = half, tp) holds tile
+        // 2 tp + half's two values.  A pass-1 key is within E16 of the exact key,
+        // so a 32-point half whose values all exceed its points' tau + E16 + E2
+        // (pass-2 keys then exceed tau) has no candidate in that tile, and pass 2
+        // leaves the tile out for it.
+        auto tile_word = [&](int half, int tp) -> unsigned & { return bitsL[((half * W + tp) * 32 + i32) * 2 + h]; };
+        auto screen_pass1_tiles = [&](auto in_lds, const void *Aglob) {
+            const void *Ab = decltype(in_lds)::value ? static_cast<const void *>(tilesL) : Aglob;
             const float *Nb = decltype(in_lds)::value ? normsL : a.norms;
-            TileRegs<1, DC> Th, Tl;
+            TileRegs<1, DC> T;
             for (int tp = 0; tp < W; ++tp) {
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
-                    const int t = 2 * tp + half;
                     f32x16 acc[2];
-                    load_tile<1, DC>(Ab, t, lane, Th);
-                    screen_tile<1, DC>(Nb, t, lane, Th, P16, acc);
-                    bool need[2];
+                    load_tile<1, DC>(Ab, 2 * tp + half, lane, T);
+                    screen_tile<1, DC>(Nb, 2 * tp + half, lane, T, P16, acc);
+                    pass1_consume(acc, half);
+                    unsigned v[2];
 #pragma unroll
                     for (int p = 0; p < 2; ++p) {
                         float m = acc[p][0];
 #pragma unroll
                         for (int r = 1; r < 16; ++r) m = vmin32(m, acc[p][r], ninf);
-                        need[p] = __ballot(m <= thr[p]) != 0ull;
+                        v[p] = (unsigned)max(__float_as_int(m + xnp[p]), 0);
                     }
-                    if (need[0] || need[1]) {
-                        load_tile<1, DC>(a.A16, t, lane, Tl);
+                    tile_word(half, tp) = (v[0] >> 16) | (v[1] & 0xFFFF0000u);
+                }
+            }
+        };
+        // pass 2 over the tiles that may hold candidates; thr16: tau + E16 + E2
+        // as an approximate delta^2, its upper 16 bits (rounding is monotone, so
+        // a larger stored value means a larger key)
+        auto screen_pass2_tiles = [&](auto in_lds, const auto &P32, auto consume, auto store,
+                                      const unsigned (&thr16)[2]) {
+            const void *Ab = decltype(in_lds)::value ? static_cast<const void *>(tilesL) : a.A;
+            const float *Nb = decltype(in_lds)::value ? normsL : a.norms;
+            for (int tp = 0; tp < W; ++tp) {
+                bool need[2][2];
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    const unsigned v = tile_word(half, tp);
+                    need[half][0] = __ballot((v & 0xFFFFu) <= thr16[0]) != 0ull;
+                    need[half][1] = __ballot((v >> 16) <= thr16[1]) != 0ull;
+                }
+                if (!(need[0][0] || need[0][1] || need[1][0] || need[1][1])) continue;  // the masks leave these words out
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    const int t = 2 * tp + half;
+                    f32x16 acc[2];
+                    if (need[half][0] || need[half][1]) {
+                        const float4 *np = reinterpret_cast<const float4 *>(Nb + (size_t)(t * 2 + (lane >> 5)) * 16);
+                        float4 n[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) n[i] = np[i];
+                        TileRegs<MODE, DC> T;
+                        TileRegs<1, DC> Tl;  // BF16 mode: the low parts
+                        load_tile<MODE, DC>(Ab, t, lane, T);
+                        if constexpr (MODE == 1) load_tile<1, DC>(a.A16, t, lane, Tl);
 #pragma unroll
                         for (int p = 0; p < 2; ++p) {
-                            if (need[p]) {
+                            if (!need[half][p]) continue;
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                acc[p][4 * i] = n[i].x;
+                                acc[p][4 * i + 1] = n[i].y;
+                                acc[p][4 * i + 2] = n[i].z;
+                                acc[p][4 * i + 3] = n[i].w;
+                            }
+                            if constexpr (MODE == 1) {
 #pragma unroll
                                 for (int c = 0; c < DC; ++c) {
                                     const bf16x8 al = __builtin_bit_cast(bf16x8, Tl.a[c]);
-                                    const bf16x8 ah = __builtin_bit_cast(bf16x8, Th.a[c]);
+                                    const bf16x8 ah = __builtin_bit_cast(bf16x8, T.a[c]);
                                     acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, P16.b[p][c], acc[p], 0, 0, 0);
                                     acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, P16lo.b[p][c], acc[p], 0, 0, 0);
+                                    acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, P16.b[p][c], acc[p], 0, 0, 0);
                                 }
-                            }
-                        }
-                    }
-                    consume(acc, need);
-                }
-                store(tp);
-            }
-        };
-        // FP32 mode's pass 2 likewise, for points in locality order: the BF16
-        // key (the pass-1 key, again) decides whether a half needs the tile's
-        // FP32 products.
-        auto screen_pass_fp32_skip = [&](auto in_lds, const auto &P32, auto consume, auto store,
-                                         const float (&thr)[2]) {
-            const void *Ab = decltype(in_lds)::value ? static_cast<const void *>(tilesL) : a.A;
-            const float *Nb = decltype(in_lds)::value ? normsL : a.norms;
-            TileRegs<1, DC> T16;
-            TileRegs<0, DC> T32;
-            for (int tp = 0; tp < W; ++tp) {
-#pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    const int t = 2 * tp + half;
-                    f32x16 acc[2];
-                    load_tile<1, DC>(a.A16, t, lane, T16);
-                    screen_tile<1, DC>(a.norms, t, lane, T16, P16, acc);
-                    bool need[2];
-#pragma unroll
-                    for (int p = 0; p < 2; ++p) {
-                        float m = acc[p][0];
-#pragma unroll
-                        for (int r = 1; r < 16; ++r) m = vmin32(m, acc[p][r], ninf);
-                        need[p] = __ballot(m <= thr[p]) != 0ull;
-                    }
-                    if (need[0] || need[1]) {
-                        load_tile<0, DC>(Ab, t, lane, T32);
-                        const float4 *np = reinterpret_cast<const float4 *>(Nb + (size_t)(t * 2 + (lane >> 5)) * 16);
-#pragma unroll
-                        for (int p = 0; p < 2; ++p) {
-                            if (need[p]) {
-#pragma unroll
-                                for (int i = 0; i < 4; ++i) {
-                                    const float4 n = np[i];
-                                    acc[p][4 * i] = n.x;
-                                    acc[p][4 * i + 1] = n.y;
-                                    acc[p][4 * i + 2] = n.z;
-                                    acc[p][4 * i + 3] = n.w;
-                                }
+                            } else {
 #pragma unroll
                                 for (int s = 0; s < 8 * DC; ++s)
-                                    acc[p] = __builtin_amdgcn_mfma_f32_32x32x2f32(T32.a[s], P32.b[p][s], acc[p], 0, 0, 0);
+                                    acc[p] = __builtin_amdgcn_mfma_f32_32x32x2f32(T.a[s], P32.b[p][s], acc[p], 0, 0, 0);
                             }
                         }
                     }
-                    consume(acc, need);
+                    consume(acc, need[half]);
                 }
                 store(tp);
             }
         };
         {
             auto no_store = [](int) {};
-            if constexpr (MODE == 1) {
+            if (a.pt_order) {
+                // (FP32 mode: the LDS copy holds the FP32 tiles of pass 2)
+                if constexpr (MODE == 1) {
+                    if (a.lds_tiles)
+                        screen_pass1_tiles(BoolTag<true>{}, a.A);
+                    else
+                        screen_pass1_tiles(BoolTag<false>{}, a.A);
+                } else {
+                    screen_pass1_tiles(BoolTag<false>{}, a.A16);
+                }
+            } else if constexpr (MODE == 1) {
                 if (a.lds_tiles)
                     screen_pass(BoolTag<true>{}, IntTag<1>{}, P16, a.A, pass1_consume, no_store);
                 else
@@ -1290,44 +1298,29 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                     }
                 }
             };
-            // the skip threshold tau + E16 + E2, rounded up
-            float thr[2];
+            if (a.pt_order) {
+                // tau + E16 + E2, rounded up, as an approximate delta^2
+                unsigned thr16[2];
 #pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const float w = e16[p] + e2[p];
-                thr[p] = (tau[p] + w) + 4.f * U32 * (fabsf(tau[p]) + w);
-            }
-            if constexpr (MODE == 1) {
-                if (a.pt_order) {
-                    if (a.lds_tiles)
-                        screen_pass_split_skip(BoolTag<true>{}, pass2_consume_skip, pass2_store, thr);
-                    else
-                        screen_pass_split_skip(BoolTag<false>{}, pass2_consume_skip, pass2_store, thr);
-                } else if (a.lds_tiles) {
+                for (int p = 0; p < 2; ++p) {
+                    const float w = e16[p] + e2[p];
+                    const float thr = (tau[p] + w) + 4.f * U32 * (fabsf(tau[p]) + w);
+                    thr16[p] = (unsigned)max(__float_as_int(thr + xnp[p]), 0) >> 16;
+                }
+                if (a.lds_tiles)
+                    screen_pass2_tiles(BoolTag<true>{}, P32, pass2_consume_skip, pass2_store, thr16);
+                else
+                    screen_pass2_tiles(BoolTag<false>{}, P32, pass2_consume_skip, pass2_store, thr16);
+            } else if constexpr (MODE == 1) {
+                if (a.lds_tiles)
                     screen_pass_split(BoolTag<true>{}, pass2_consume, pass2_store);
-                } else {
+                else
                     screen_pass_split(BoolTag<false>{}, pass2_consume, pass2_store);
-                }
             } else {
-                // (FP32 mode skips from 48 padded dimensions on, where the FP32
-                // products cost most; below, the BF16 operand is not kept live
-                // through pass 2, which leaves the 12-wave blocks their registers)
-                bool done = false;
-                if constexpr (DC >= 3) {
-                    if (a.pt_order) {
-                        if (a.lds_tiles)
-                            screen_pass_fp32_skip(BoolTag<true>{}, P32, pass2_consume_skip, pass2_store, thr);
-                        else
-                            screen_pass_fp32_skip(BoolTag<false>{}, P32, pass2_consume_skip, pass2_store, thr);
-                        done = true;
-                    }
-                }
-                if (!done) {
-                    if (a.lds_tiles)
-                        screen_pass(BoolTag<true>{}, IntTag<0>{}, P32, a.A, pass2_consume, pass2_store);
-                    else
-                        screen_pass(BoolTag<false>{}, IntTag<0>{}, P32, a.A, pass2_consume, pass2_store);
-                }
+                if (a.lds_tiles)
+                    screen_pass(BoolTag<true>{}, IntTag<0>{}, P32, a.A, pass2_consume, pass2_store);
+                else
+                    screen_pass(BoolTag<false>{}, IntTag<0>{}, P32, a.A, pass2_consume, pass2_store);
             }
         }
         // Certificate bound per point: a non-candidate's exact distance^2

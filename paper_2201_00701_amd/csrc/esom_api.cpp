@@ -120,9 +120,7 @@ size_t carve(Scratch &sc, void *base, int64_t n, int g, int dp, int pg, int64_t 
     sc.fb_list = static_cast<int32_t *>(take(sizeof(int32_t) * (size_t)(n > 0 ? n : 1)));
     sc.fb_reason = static_cast<uint8_t *>(take((size_t)(n > 0 ? n : 1)));
     sc.fb_thresh = static_cast<float *>(take(sizeof(float) * (size_t)(n > 0 ? n : 1)));
-    sc.pt_cell = static_cast<uint8_t *>(take((size_t)(n > 0 ? n : 1)));
     sc.pt_order = static_cast<int32_t *>(take(sizeof(int32_t) * (size_t)(n > 0 ? n : 1)));
-    sc.bin_hist = static_cast<unsigned *>(take(sizeof(unsigned) * 128));
     sc.mat_cap = mat_n;
     if (mat_n > 0) {
         sc.mat_keys = static_cast<float *>(take(sizeof(float) * (size_t)mat_n * ntiles * TILE));
@@ -284,8 +282,8 @@ int enqueue_embed(Scratch &sc, unsigned long long *counters, int num_cus, size_t
         bb.dp = pl.dp;
         bb.g = g;
         bb.L = L;
-        bb.hist = sc.bin_hist;
-        bb.cell = sc.pt_cell;
+        bb.hist = sc.bin_hist();
+        bb.cell = sc.pt_cell();
         bb.order = sc.pt_order;
         bb.x_vec4 = (d == pl.dp && ldx % 4 == 0 && ((uintptr_t)Xc & 15) == 0) ? 1 : 0;
         return bb;
@@ -709,16 +707,16 @@ int esom_embed_noalloc(const float *X, int64_t n, int32_t d, int64_t ldx, const 
     std::call_once(nd.once, noalloc_setup, std::ref(nd));
     if (nd.err != hipSuccess) return hip_fail(nd.err, "allocation-free scratch set-up");
     // Layout: counters, then the embed scratch for `chunk` points.  Every
-    // chunk point adds 4 + 1 + 4 bytes to the exact-path list and 1 + 4 to
-    // the locality order; with chunk a multiple of 256 those five arrays need
-    // no alignment padding beyond what carve reserves for one point each.
+    // chunk point adds 4 + 1 + 4 bytes to the exact-path list and 4 to the
+    // locality order; with chunk a multiple of 256 those four arrays need no
+    // alignment padding beyond what carve reserves for one point each.
     const Plan pl = make_plan(d, g, P.k, P.mode, P.candidates);
     const int pg = embed_needs_pairs(d, g, P, EMBED_FULL) ? g : 0;
     const size_t room = ESOM_NOALLOC_SCRATCH_BYTES - NOALLOC_COUNTER_BYTES;
     Scratch sc;
     const size_t fixed = carve(sc, nullptr, 1, g, pl.dp, pg);
-    if (fixed + 14 * 256 > room) return fail(ESOM_EINVAL, "landmark set too large for the allocation-free scratch");
-    int64_t chunk = (int64_t)((room - fixed) / 14) & ~(int64_t)255;
+    if (fixed + 13 * 256 > room) return fail(ESOM_EINVAL, "landmark set too large for the allocation-free scratch");
+    int64_t chunk = (int64_t)((room - fixed) / 13) & ~(int64_t)255;
     if (chunk > n) chunk = n;
     if (carve(sc, nullptr, chunk, g, pl.dp, pg) > room)
         return fail(ESOM_EINVAL, "internal: allocation-free scratch layout overflow");

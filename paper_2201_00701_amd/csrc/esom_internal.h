@@ -73,10 +73,12 @@ struct Scratch {
     int32_t *mat_idx = nullptr;     // mat_cap x k
     float *mat_d2 = nullptr;        // mat_cap x k
     uint8_t *mat_mark = nullptr;    // mat_cap
-    // locality order of the points (esom_bin.hip), for cap_n points
-    uint8_t *pt_cell = nullptr;     // nearest pivot's place per point
+    // locality order of the points (esom_bin.hip), for cap_n points.  Its bins
+    // (pt_cell) and counters (bin_hist) are done with before the fused kernel
+    // starts to list points, so they share the list's arrays.
     int32_t *pt_order = nullptr;    // processing order: slot -> point
-    unsigned *bin_hist = nullptr;   // 2 x 64: points per pivot, then placement cursors
+    uint16_t *pt_cell() const { return reinterpret_cast<uint16_t *>(fb_thresh); }
+    unsigned *bin_hist() const { return reinterpret_cast<unsigned *>(fb_reason); }
     // the locality order runs on a second stream beside the landmark
     // preparation when the context has one (none: on the call's stream)
     hipStream_t side = nullptr;
@@ -127,18 +129,20 @@ struct EmbedArgs {
 
 // Locality order of the points (esom_bin.hip): each point's nearest of the
 // 64 ordering pivots (landmarks j g / 64, BF16 MFMA keys centred on landmark
-// 0), then a counting sort by pivot.  Needs nothing from the landmark
+// 0) and a class of its distance, then a counting sort by both.  Needs nothing from the landmark
 // preparation, so it can run beside it.  Used for large landmark sets
 // (g >= BIN_MIN_G) and calls of at least BIN_MIN_N points.
 constexpr int BIN_MIN_G = 512;
 constexpr int64_t BIN_MIN_N = 65536;
+constexpr int BIN_COUNT = 512;  // bins: 64 pivots x 8 distance classes
+static_assert(BIN_MIN_N >= (int64_t)sizeof(unsigned) * 2 * BIN_COUNT, "the counters fit in the reason flags");
 struct BinArgs {
     const float *X;
     int64_t n, ldx;
     int d, dp, g;
     const float *L;
-    unsigned *hist;        // 2 x 64 (zeroed by launch_bin)
-    uint8_t *cell;         // n
+    unsigned *hist;        // 2 x BIN_COUNT: points per bin, then placement cursors (zeroed by launch_bin)
+    uint16_t *cell;        // n
     int32_t *order;        // n
     int x_vec4;            // 1: d == dp, X 16-byte aligned, ldx % 4 == 0
 };

@@ -309,6 +309,18 @@ __device__ __forceinline__ double vmax64(double a, double b) {
     return r;
 }
 
+// The value of lane S of the calling lane's quad, and the sum over a quad (the
+// same on its four lanes).  All lanes of the wavefront take part.
+template <int S>
+__device__ __forceinline__ int quad_bcast(int v) {
+    return __builtin_amdgcn_mov_dpp(v, S * 0x55, 0xf, 0xf, true);
+}
+__device__ __forceinline__ float quad_sum(float v) {
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xf, 0xf, true));  // lanes 1 0 3 2
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xf, 0xf, true));  // lanes 2 3 0 1
+    return v;
+}
+
 // Insert v into the ascending list s; whatever falls off the end updates rej
 // (the smallest key ever rejected).
 template <int KP>
@@ -1350,8 +1362,16 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
         const bool valid = pbase + lane < a.n;
         const int64_t pi = valid ? slot_point(a, pbase + lane) : 0;  // the point's own index
         const float cert_rhs = certL[lane];
+        // The point's row.  ROWS = 1: in the lane's registers.  ROWS = 0 (landmark
+        // rows from memory): the four lanes of a quad rescore one candidate at a
+        // time together, each on every fourth float4 of the rows, so x holds this
+        // lane's pieces of its quad's four points: [4 c + 4 DC s ...] the
+        // dimensions 16 c + 4 (lane mod 4) of the point of the quad's lane s.  A
+        // load then covers 16 rows with 64 consecutive bytes each instead of 64
+        // rows with 16: the kernel was bound by the L1's line accesses (0.92 a
+        // clock at 1M x 48-D with 1024 landmarks, half of them the walk's).
         float x[DP];
-        {
+        if constexpr (ROWS == 1) {
             const float *xr = a.X + (valid ? pi : 0) * a.ldx;
             if (a.x_vec4) {
 #pragma unroll
@@ -1366,6 +1386,31 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
 #pragma unroll
                 for (int t = 0; t < DP; ++t) x[t] = (t < a.d) ? xr[t < a.d ? t : a.d - 1] : 0.f;
             }
+        } else {
+            const int pq = (int)(valid ? pi : 0);
+            auto load_quad = [&](auto st) {
+                constexpr int S = decltype(st)::value;
+                const float *xr = a.X + (int64_t)quad_bcast<S>(pq) * a.ldx;
+#pragma unroll
+                for (int c = 0; c < DC; ++c) {
+                    float *xc = x + 4 * (c + DC * S);
+                    const int t0 = 16 * c + 4 * (lane & 3);
+                    if (a.x_vec4) {
+                        const float4 v = *reinterpret_cast<const float4 *>(xr + t0);
+                        xc[0] = v.x;
+                        xc[1] = v.y;
+                        xc[2] = v.z;
+                        xc[3] = v.w;
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) xc[e] = t0 + e < a.d ? xr[t0 + e] : 0.f;
+                    }
+                }
+            };
+            load_quad(IntTag<0>{});
+            load_quad(IntTag<1>{});
+            load_quad(IntTag<2>{});
+            load_quad(IntTag<3>{});
         }
         double sk[KP];
 #pragma unroll
@@ -1398,24 +1443,50 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                 // bit 32 h + pos of a word of tile pair ctp: position 64 ctp + 2 pos + h
                 const int j = act ? 64 * ctp + 2 * (bit & 31) + (bit >> 5) : 0;
                 float acc = 0.f;
-                // rows from the block's LDS copy or from global memory (separate
-                // code, so that each load has its own address space)
-                auto add_row = [&](const float4 lv, int q) {
-                    const float e0 = x[4 * q] - lv.x, e1 = x[4 * q + 1] - lv.y;
-                    const float e2 = x[4 * q + 2] - lv.z, e3 = x[4 * q + 3] - lv.w;
-                    acc = fmaf(e0, e0, acc);
-                    acc = fmaf(e1, e1, acc);
-                    acc = fmaf(e2, e2, acc);
-                    acc = fmaf(e3, e3, acc);
+                auto add4 = [](float &sum, const float *xv, const float4 lv) {
+                    const float e0 = xv[0] - lv.x, e1 = xv[1] - lv.y;
+                    const float e2 = xv[2] - lv.z, e3 = xv[3] - lv.w;
+                    sum = fmaf(e0, e0, sum);
+                    sum = fmaf(e1, e1, sum);
+                    sum = fmaf(e2, e2, sum);
+                    sum = fmaf(e3, e3, sum);
                 };
+                // rows from the block's LDS copy, or by quads from memory
                 if constexpr (ROWS == 1) {
                     const float4 *Lr = reinterpret_cast<const float4 *>(rowsL + row_offset<RS>(j));
 #pragma unroll
-                    for (int q = 0; q < DP / 4; ++q) add_row(Lr[q], q);
+                    for (int q = 0; q < DP / 4; ++q) add4(acc, x + 4 * q, Lr[q]);
                 } else {
-                    const float4 *Lr = reinterpret_cast<const float4 *>(a.Lpad + (size_t)j * DP);
+                    const char *base = reinterpret_cast<const char *>(a.Lpad);
+                    const unsigned off = mul24((unsigned)j, 4u * DP);
+                    const unsigned o[4] = {(unsigned)quad_bcast<0>((int)off) + 16u * (lane & 3),
+                                           (unsigned)quad_bcast<1>((int)off) + 16u * (lane & 3),
+                                           (unsigned)quad_bcast<2>((int)off) + 16u * (lane & 3),
+                                           (unsigned)quad_bcast<3>((int)off) + 16u * (lane & 3)};
+                    // The loads go through the four candidates' rows 64 bytes at
+                    // a time, so that a line's second half follows its first
+                    // after 64 other accesses: an access to a line still on its
+                    // way stalls the L1 (row by row, its pending-stall cycles
+                    // doubled and the fused kernel took 1.010 ms at 1M x 48-D;
+                    // in this order 0.790 ms, lane by lane 0.896 ms, and at 10M
+                    // x 64-D 8.25 against 10.26 ms).
+                    float4 lv[DC][4];
 #pragma unroll
-                    for (int q = 0; q < DP / 4; ++q) add_row(Lr[q], q);
+                    for (int c = 0; c < DC; ++c)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            lv[c][q] = *reinterpret_cast<const float4 *>(base + (size_t)(o[q] + 64u * c));
+                    __builtin_amdgcn_sched_barrier(0);
+                    float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int c = 0; c < DC; ++c)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) add4(sum[q], x + 4 * (c + DC * q), lv[c][q]);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float t = quad_sum(sum[q]);
+                        acc = (lane & 3) == q ? t : acc;
+                    }
                 }
                 // keys carry the landmark index (ties break on it), not the position
                 insert_sorted<KP>(sk, rej, act ? pack_key(acc, permL[j]) : (double)INFINITY);
@@ -1469,8 +1540,8 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
         int nref = 0;
         if constexpr (KP <= 8) {
             if (!a.knn_only) {
-                // rows of more than 64 dimensions are read again from memory
-                // instead of being kept in registers past the walk
+                // rows of more than 64 dimensions, or held by quads, are read
+                // again from memory
                 const float *xr = a.X + (valid ? pi : 0) * a.ldx;
                 auto d2x = [&](int jl) -> double {
                     const unsigned pos = iposL[jl];
@@ -1487,7 +1558,7 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                         acc = fma(e2, e2, acc);
                         acc = fma(e3, e3, acc);
                     };
-                    if constexpr (DC <= 4) {
+                    if constexpr (DC <= 4 && ROWS == 1) {
 #pragma unroll
                         for (int q = 0; q < DP / 4; ++q)
                             add4(make_float4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]), Lr[q]);

@@ -44,6 +44,8 @@ namespace esom {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float U32 = 5.9604645e-08f;     // 2^-24, FP32 unit roundoff
@@ -94,6 +96,14 @@ __device__ __forceinline__ unsigned bf16_bits_rne(float f) {
     u += 0x7FFFu + ((u >> 16) & 1u);
     return u >> 16;
 }
+
+// Two floats rounded to BF16 (to nearest even), the first in the low half.
+__device__ __forceinline__ unsigned bf16_pair(float a, float b) {
+    const f32x2 v = {a, b};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+}
+__device__ __forceinline__ float bf16_lo(unsigned w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf16_hi(unsigned w) { return __uint_as_float(w & 0xFFFF0000u); }
 
 __device__ __forceinline__ double pack_key(float d2, int j) {
     unsigned long long b = (unsigned long long)__double_as_longlong((double)d2);
@@ -220,6 +230,42 @@ __device__ __forceinline__ int select_pair_jth(int (&lo)[16], int (&hi)[16], int
     return t;
 }
 
+// An upper bound of the J-th smallest (compile-time, 8 <= J <= 24) of those 64
+// values, the same on both lanes: the J-th smallest of the two lanes' M smallest
+// (M = 8 or 16), which is the J-th of all unless one lane holds more than M of
+// them (possible for J > M only).  With two ascending lists s and t the J-th
+// smallest of their union is the minimum over a + b = J of max(s_a, t_b) (s_0 =
+// t_0 = -inf), so the two lanes' lists need no merge.  About 400 instructions
+// for J = 16 and 20 where select_pair_jth takes 460 and 820 (1M x 48-D, k = 20:
+// with the conversion instructions for the operands, fused kernel 0.790 ->
+// 0.744 ms; 10M x 64-D 8.4 -> 7.85 ms).
+template <int J>
+__device__ __forceinline__ int select_pair_static(int (&lo)[16], int (&hi)[16]) {
+    constexpr int M = J <= 8 ? 8 : 16;
+    static_assert(J <= 24 && J <= 2 * M, "list length");
+    sort_regs<16>(lo);
+    sort_regs<16>(hi);
+    int s[M];
+#pragma unroll
+    for (int i = 0; i < M; ++i) s[i] = min(lo[i], hi[M - 1 - i]);
+    bitonic_clean<M>(s);
+    int u[M], v[M];  // the lower and the upper lane's lists, on both
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+        const auto r = __builtin_amdgcn_permlane32_swap((unsigned)s[i], (unsigned)s[i], false, false);
+        u[i] = (int)r[0];
+        v[i] = (int)r[1];
+    }
+    int t = 0x7FFFFFFF;
+#pragma unroll
+    for (int i = 0; i <= M; ++i) {  // i values of the first list, J - i of the second
+        if (J - i < 0 || J - i > M) continue;
+        const int x = i == 0 ? v[J - 1] : J - i == 0 ? u[i - 1] : max(u[i > 0 ? i - 1 : 0], v[J - i > 0 ? J - i - 1 : 0]);
+        t = min(t, x);
+    }
+    return t;
+}
+
 // The j-th smallest (1 <= j <= 32) of the 32 values lo[0..15], hi[0..15].
 // For j <= 16: with both halves sorted, min(lo[i], hi[15 - i]) holds the 16
 // smallest of the union as a bitonic sequence; its maximum is the 16th
@@ -288,6 +334,14 @@ __device__ __forceinline__ unsigned row_offset(int j) {
     return mul24((unsigned)j, (unsigned)RS);
 }
 
+// Orders this wavefront's LDS accesses before and after it (its lanes exchange
+// data through LDS; the hardware keeps a wavefront's LDS accesses in order).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // -inf in a scalar register, opaque to the compiler.
 __device__ __forceinline__ float opaque_neg_inf() {
     float r;
@@ -320,6 +374,16 @@ __device__ __forceinline__ float quad_sum(float v) {
     v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xf, 0xf, true));  // lanes 2 3 0 1
     return v;
 }
+
+// The value of lane U of the calling lane's row of 16 lanes.
+template <int U>
+__device__ __forceinline__ unsigned row16_bcast(unsigned v) {
+    return (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x150 + U, 0xf, 0xf, true);
+}
+
+// f(IntTag<A>{}), ..., f(IntTag<B - 1>{})
+template <int A, int B, class F>
+__device__ __forceinline__ void static_for(F &&f);
 
 // Insert v into the ascending list s; whatever falls off the end updates rej
 // (the smallest key ever rejected).
@@ -355,6 +419,18 @@ template <int V>
 struct IntTag {
     static constexpr int value = V;
 };
+template <int A, int B, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+    if constexpr (A < B) {
+        f(IntTag<A>{});
+        static_for<A + 1, B>(f);
+    }
+}
+
+// LDS of the pair loop at KP = 16: a row of pair-table entries per point, the
+// stride of 20 floats free of bank conflicts for 16-byte reads.
+constexpr int PAIR_STRIDE = 20;
+constexpr int PAIR_LDS_BYTES = 64 * PAIR_STRIDE * 4;
 
 // LDS bytes of the block-wide centroid copy (padded dimension <= 128).
 constexpr int CENT_LDS_BYTES = 512;
@@ -379,7 +455,9 @@ __host__ __device__ inline size_t tile_lds_bytes(int mode, int ntiles, int dc) {
 __host__ __device__ inline int wave_smem_bytes(int kp, int k, int npair_tiles) {
     const int bits = 2 * npair_tiles * 64 * 4;
     const int nbr = kp > 24 ? k * 64 * 10 : 0;
-    return (bits > nbr ? bits : nbr) + 512 + 1024;
+    const int all = (bits > nbr ? bits : nbr) + 512 + 1024;
+    // (kp = 16: the pair loop's rows, once the rest is done with)
+    return kp == 16 && all < PAIR_LDS_BYTES ? PAIR_LDS_BYTES : all;
 }
 
 // Centred values x_t - c_t of dimensions 16 c + 8 h + e (e < 8) of the point
@@ -408,8 +486,9 @@ __device__ __forceinline__ void centred8(const EmbedArgs &a, const float *xr, co
 }
 
 // Point index of processing slot si < n (the optional locality order).
+template <int ROWS>
 __device__ __forceinline__ int64_t slot_point(const EmbedArgs &a, int64_t si) {
-    return a.pt_order ? (int64_t)a.pt_order[si] : si;
+    return ROWS == 0 && a.pt_order ? (int64_t)a.pt_order[si] : si;
 }
 
 template <int MODE, int DC>
@@ -679,20 +758,24 @@ __device__ __forceinline__ unsigned project_point(const EmbedArgs &a, const doub
         const float ihh = (inv > 0.f && hh > 0.f) ? __builtin_amdgcn_rcpf(hh) : 0.f;
         const float D = fmaf(d2i - d2j, inv, 0.5f);
         pmax = fmaxf(pmax, d2j * inv);
-        float q;
+        // n = h / |h|^2: M += s_j n n^T, r += s_j D n (times |h|^(2 - 2 adjust))
+        const float nx = hx * ihh, ny = hy * ihh;
+        float tx, ty;
         // unit: adjust == 1 (weight 1 / |h|^2), as a compile-time tag so that
         // the two variants of the pair loop are separate code
-        if constexpr (decltype(unit)::value)
-            q = sj * ihh;
-        else
-            q = ihh > 0.f ? sj * exp2f(a.adjust * __log2f(ihh)) : 0.f;
-        const float qh = q * ihh, qD = q * D;
-        const float qhx = qh * hx, qhy = qh * hy;
-        Mi[0] = fmaf(qhx, hx, Mi[0]);
-        Mi[1] = fmaf(qhx, hy, Mi[1]);
-        Mi[2] = fmaf(qhy, hy, Mi[2]);
-        ri[0] = fmaf(qD, hx, ri[0]);
-        ri[1] = fmaf(qD, hy, ri[1]);
+        if constexpr (decltype(unit)::value) {
+            tx = sj * nx;
+            ty = sj * ny;
+        } else {
+            const float q = ihh > 0.f ? sj * exp2f(a.adjust * __log2f(ihh)) : 0.f;
+            tx = q * hx;
+            ty = q * hy;
+        }
+        Mi[0] = fmaf(tx, nx, Mi[0]);
+        Mi[1] = fmaf(tx, ny, Mi[1]);
+        Mi[2] = fmaf(ty, ny, Mi[2]);
+        ri[0] = fmaf(tx, D, ri[0]);
+        ri[1] = fmaf(ty, D, ri[1]);
     };
     // closes base i: r += s_i (r_i + M_i l_i), M += s_i M_i
     auto close_base = [&](bool origin, float si, float lxi, float lyi, const float (&Mi)[3],
@@ -708,7 +791,85 @@ __device__ __forceinline__ unsigned project_point(const EmbedArgs &a, const doub
         r1 = fmaf(si, ri[1], r1);
     };
     auto run_pairs = [&](auto unit) {
-    if constexpr (KP <= 24) {
+    if constexpr (KP == 16) {
+        // The pair-table reads by 16 lanes a point, four points a load.  Step t
+        // reads the rows of bases t and 14 - t, which have 16 entries together:
+        // lane v > t the entry (t, v), lane v <= t the entry (14 - t, 15 - v).  The
+        // neighbours sit close together in the landmark order, so a point's
+        // entries of a row fall into two or three lines, which this asks for once;
+        // a lane that read its own point's entries one by one asked for them
+        // 15 - u times, mostly while they were still on their way.  The entries
+        // go through LDS to their points' lanes, one step ahead of use.  At 1M x
+        // 32-D the L1's line accesses fell from 159M to 136M a call; the address
+        // arithmetic takes back most of it there (0.5 to 1% faster), projections
+        // from cached neighbours are 4% faster.
+        const char *ptab = reinterpret_cast<const char *>(a.pairs);
+        float *rows = nbD2;  // 64 x PAIR_STRIDE
+        const int v16 = lane & 15;
+        unsigned col[16];    // 4 x position of neighbour v16 of point 4 G + (lane / 16)
+        {
+            unsigned *pk = reinterpret_cast<unsigned *>(rows);  // 64 x 16 positions of 16 bits
+            const unsigned p0 = iposL[jq[0]];
+#pragma unroll
+            for (int q = 0; q < 16; q += 2) {
+                // slots past the active neighbours repeat the first
+                const unsigned lo = q < a.kact ? iposL[jq[q]] : p0, hi = q + 1 < a.kact ? iposL[jq[q + 1]] : p0;
+                pk[lane * 8 + q / 2] = lo | (hi << 16);
+            }
+            wave_lds_fence();
+            const unsigned short *ps = reinterpret_cast<const unsigned short *>(rows) + lane;
+#pragma unroll
+            for (int G = 0; G < 16; ++G) col[G] = 4u * ps[64 * G];
+            wave_lds_fence();
+        }
+        float ld[16];
+        auto fetch = [&](auto tt) {
+            constexpr int T = decltype(tt)::value;
+            const bool up = v16 > T;
+#pragma unroll
+            for (int G = 0; G < 16; ++G) {
+                const unsigned rt = row16_bcast<T>(col[G]), rm = row16_bcast<14 - T>(col[G]);
+                const unsigned cm = (unsigned)__builtin_amdgcn_mov_dpp((int)col[G], 0x140, 0xf, 0xf, true);  // lane 15 - v
+                ld[G] = *reinterpret_cast<const float *>(
+                    ptab + (size_t)(__umul24(up ? rt : rm, (unsigned)a.g) + (up ? col[G] : cm)));
+            }
+        };
+        fetch(IntTag<0>{});
+        float *wr = rows + (lane >> 4) * PAIR_STRIDE + v16;
+        const float4 *rd = reinterpret_cast<const float4 *>(rows + lane * PAIR_STRIDE);
+        static_for<0, 8>([&](auto tt) {
+            constexpr int T = decltype(tt)::value;
+#pragma unroll
+            for (int G = 0; G < 16; ++G) wr[4 * G * PAIR_STRIDE] = ld[G];
+            wave_lds_fence();
+            if constexpr (T + 1 < 8) fetch(IntTag<T + 1>{});
+            float pv[16];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float4 v = rd[i];
+                pv[4 * i] = v.x;
+                pv[4 * i + 1] = v.y;
+                pv[4 * i + 2] = v.z;
+                pv[4 * i + 3] = v.w;
+            }
+            wave_lds_fence();
+            auto base = [&](auto ut) {
+                constexpr int U = decltype(ut)::value;
+                if (U < a.kact - 1) {
+                    float Mi[3] = {0.f, 0.f, 0.f}, ri[2] = {0.f, 0.f};
+#pragma unroll
+                    for (int qj = U + 1; qj < 16; ++qj)
+                        if (qj < a.kact)
+                            pair_term(unit, d2q[U], lxq[U], lyq[U], d2q[qj], sq[qj], lxq[qj], lyq[qj],
+                                      pv[U == T ? qj : 15 - qj], Mi, ri);
+                    // neighbour 0 is the origin of the 2-D frame
+                    close_base(U == 0, sq[U], lxq[U], lyq[U], Mi, ri);
+                }
+            };
+            base(tt);
+            if constexpr (T < 7) base(IntTag<14 - T>{});
+        });
+    } else if constexpr (KP <= 24) {
         // neighbour data in registers (fully unrolled: 276 pair slots at
         // k <= 24, which ran 6% faster at 1M x 48-D, 1024 landmarks, k = 20
         // than the LDS staging below); each row of pair-table loads is issued
@@ -939,6 +1100,8 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
     float *certL = reinterpret_cast<float *>(wsm + tail);  // 64 certificate bounds (512 B reserved)
     unsigned long long *maskL = reinterpret_cast<unsigned long long *>(certL + 128);
 
+    // points in locality order (launched with ROWS = 0 and no LDS tiles)
+    const bool ordered = ROWS == 0 && a.pt_order;
     const float lmax = a.lmax[0];
     const float qa = a.lmax[1];  // max_j |bf16(-2 (L_j - c)) + 2 (L_j - c)|
 
@@ -955,33 +1118,53 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
         // for pass 2 afterwards.
         PointOperand<1, DC> P16, P16lo;  // P16lo: BF16 mode's pass 2
         float xnp[2], dxp[2];  // |x - c|^2 and |bf16(x - c) - (x - c)|^2
+        float nlo[2], nre[2];  // BF16 mode: |lo| and |r| of the split (see e2)
+        // Low parts of two split values from their remainders after the high
+        // parts, adding to |lo|^2 and |r|^2.  BF16 mode forms them with the high
+        // parts where the registers allow holding them through pass 1 (the
+        // 12-wave blocks' do not: they read the rows again).
+        constexpr bool SPLIT_EARLY = MODE == 1 && main_max_block(MODE, DC, KP) == 512 && DC <= 4;
+        auto split_low = [](float r0, float r1, float &lsum, float &rsum) -> unsigned {
+            const unsigned lw = bf16_pair(r0, r1);
+            const float l0 = bf16_lo(lw), l1 = bf16_hi(lw);
+            lsum = fmaf(l0, l0, lsum);
+            lsum = fmaf(l1, l1, lsum);
+            rsum = fmaf(r0 - l0, r0 - l0, rsum);
+            rsum = fmaf(r1 - l1, r1 - l1, rsum);
+            return lw;
+        };
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             const int64_t si = pbase + 32 * p + i32;
             const bool valid = si < a.n;
-            const float *xr = a.X + (valid ? slot_point(a, si) : 0) * a.ldx;
-            float part = 0.f, dpart = 0.f;
+            const float *xr = a.X + (valid ? slot_point<ROWS>(a, si) : 0) * a.ldx;
+            float part = 0.f, dpart = 0.f, lpart = 0.f, rpart = 0.f;
 #pragma unroll
             for (int c = 0; c < DC; ++c) {
                 float v[8];
                 centred8(a, xr, centL, c, h, valid, v);
-                unsigned w[4];
+                unsigned w[4], lw[4];
 #pragma unroll
                 for (int e = 0; e < 8; e += 2) {
                     part = fmaf(v[e], v[e], part);
                     part = fmaf(v[e + 1], v[e + 1], part);
-                    const unsigned b0 = bf16_bits_rne(v[e]), b1 = bf16_bits_rne(v[e + 1]);
+                    const unsigned hw = bf16_pair(v[e], v[e + 1]);
                     // quantisation errors (exact in FP32)
-                    const float q0 = __uint_as_float(b0 << 16) - v[e], q1 = __uint_as_float(b1 << 16) - v[e + 1];
+                    const float q0 = v[e] - bf16_lo(hw), q1 = v[e + 1] - bf16_hi(hw);
                     dpart = fmaf(q0, q0, dpart);
                     dpart = fmaf(q1, q1, dpart);
-                    w[e >> 1] = b0 | (b1 << 16);
+                    w[e >> 1] = hw;
+                    if constexpr (SPLIT_EARLY) lw[e >> 1] = split_low(q0, q1, lpart, rpart);
                 }
-                u32x4 wv = {w[0], w[1], w[2], w[3]};
-                P16.b[p][c] = __builtin_bit_cast(bf16x8, wv);
+                P16.b[p][c] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
+                if constexpr (SPLIT_EARLY) P16lo.b[p][c] = __builtin_bit_cast(bf16x8, u32x4{lw[0], lw[1], lw[2], lw[3]});
             }
             xnp[p] = part + __shfl_xor(part, 32);
             dxp[p] = dpart + __shfl_xor(dpart, 32);
+            if constexpr (SPLIT_EARLY) {
+                nlo[p] = sqrtf(lpart + __shfl_xor(lpart, 32));
+                nre[p] = sqrtf(rpart + __shfl_xor(rpart, 32));
+            }
         }
         // Rigorous bounds of the screen's rounding error in key units, per
         // point.  With a = -2(L - c) and its BF16 image a + da, x' = x - c and
@@ -1065,9 +1248,8 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
         // (pass-2 keys then exceed tau) has no candidate in that tile, and pass 2
         // leaves the tile out for it.
         auto tile_word = [&](int half, int tp) -> unsigned & { return bitsL[((half * W + tp) * 32 + i32) * 2 + h]; };
-        auto screen_pass1_tiles = [&](auto in_lds, const void *Aglob) {
-            const void *Ab = decltype(in_lds)::value ? static_cast<const void *>(tilesL) : Aglob;
-            const float *Nb = decltype(in_lds)::value ? normsL : a.norms;
+        auto screen_pass1_tiles = [&](const void *Ab) {
+            const float *Nb = a.norms;
             TileRegs<1, DC> T;
             for (int tp = 0; tp < W; ++tp) {
 #pragma unroll
@@ -1091,10 +1273,9 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
         // pass 2 over the tiles that may hold candidates; thr16: tau + E16 + E2
         // as an approximate delta^2, its upper 16 bits (rounding is monotone, so
         // a larger stored value means a larger key)
-        auto screen_pass2_tiles = [&](auto in_lds, const auto &P32, auto consume, auto store,
-                                      const unsigned (&thr16)[2]) {
-            const void *Ab = decltype(in_lds)::value ? static_cast<const void *>(tilesL) : a.A;
-            const float *Nb = decltype(in_lds)::value ? normsL : a.norms;
+        auto screen_pass2_tiles = [&](const auto &P32, auto consume, auto store, const unsigned (&thr16)[2]) {
+            const void *Ab = a.A;
+            const float *Nb = a.norms;
             for (int tp = 0; tp < W; ++tp) {
                 bool need[2][2];
 #pragma unroll
@@ -1150,16 +1331,8 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
         };
         {
             auto no_store = [](int) {};
-            if (a.pt_order) {
-                // (FP32 mode: the LDS copy holds the FP32 tiles of pass 2)
-                if constexpr (MODE == 1) {
-                    if (a.lds_tiles)
-                        screen_pass1_tiles(BoolTag<true>{}, a.A);
-                    else
-                        screen_pass1_tiles(BoolTag<false>{}, a.A);
-                } else {
-                    screen_pass1_tiles(BoolTag<false>{}, a.A16);
-                }
+            if (ordered) {
+                if constexpr (ROWS == 0) screen_pass1_tiles(MODE == 1 ? a.A : a.A16);
             } else if constexpr (MODE == 1) {
                 if (a.lds_tiles)
                     screen_pass(BoolTag<true>{}, IntTag<1>{}, P16, a.A, pass1_consume, no_store);
@@ -1190,7 +1363,11 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                 v0[r] = max(__float_as_int(gmin[p][0][r] + xnp[p]), 0);
                 v1[r] = max(__float_as_int(gmin[p][1][r] + xnp[p]), 0);
             }
-            if (a.pair_select) {
+            // (k known at compile time and C = k, the default)
+            constexpr bool STATIC_J = KF == 1 && KP <= 24;
+            if (STATIC_J && a.pair_select && a.jsel == KP) {
+                if constexpr (STATIC_J) tbase[p] = __int_as_float(min(select_pair_static<KP>(v0, v1), 0x7F7FFFFF));
+            } else if (a.pair_select) {
                 const int tl = min(select_pair_jth(v0, v1, a.jsel), 0x7F7FFFFF);  // +inf -> FLT_MAX
                 tbase[p] = __int_as_float(tl);
             } else {
@@ -1208,43 +1385,35 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
         // a.r - ra.r + al.lo + ra.x', is at most |r| (2 max|L - c| + max|ra|) +
         // max|al| |lo| + max|ra| |x'|; the FP32 accumulation of three chains of
         // d_pad products adds (6 d_pad + 16) u (|x'| + max|L - c|)^2 (the
-        // single chain's allowance tripled).  |lo| and |r| are exact per point
-        // (the rows are read again: still in cache).  FP32 mode's FP32 operand
-        // is exact (e32).
+        // single chain's allowance tripled).  |lo| and |r| are exact per point.
+        // FP32 mode's FP32 operand is exact (e32).
         float e2[2];
         if constexpr (MODE == 1) {
             const float la = a.lmax[2], ra = a.lmax[3];
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
-                const int64_t si = pbase + 32 * p + i32;
-                const bool valid = si < a.n;
-                const float *xr = a.X + (valid ? slot_point(a, si) : 0) * a.ldx;
-                float lpart = 0.f, rpart = 0.f;
+                if constexpr (!SPLIT_EARLY) {
+                    const int64_t si = pbase + 32 * p + i32;
+                    const bool valid = si < a.n;
+                    const float *xr = a.X + (valid ? slot_point<ROWS>(a, si) : 0) * a.ldx;
+                    float lpart = 0.f, rpart = 0.f;
 #pragma unroll
-                for (int c = 0; c < DC; ++c) {
-                    float v[8];
-                    centred8(a, xr, centL, c, h, valid, v);
-                    unsigned w[4];
+                    for (int c = 0; c < DC; ++c) {
+                        float v[8];
+                        centred8(a, xr, centL, c, h, valid, v);
+                        const u32x4 hw = __builtin_bit_cast(u32x4, P16.b[p][c]);
+                        u32x4 lw;
 #pragma unroll
-                    for (int e = 0; e < 8; e += 2) {
-                        const float r0 = v[e] - __uint_as_float(bf16_bits_rne(v[e]) << 16);
-                        const float r1 = v[e + 1] - __uint_as_float(bf16_bits_rne(v[e + 1]) << 16);
-                        const unsigned b0 = bf16_bits_rne(r0), b1 = bf16_bits_rne(r1);
-                        const float l0 = __uint_as_float(b0 << 16), l1 = __uint_as_float(b1 << 16);
-                        lpart = fmaf(l0, l0, lpart);
-                        lpart = fmaf(l1, l1, lpart);
-                        rpart = fmaf(r0 - l0, r0 - l0, rpart);
-                        rpart = fmaf(r1 - l1, r1 - l1, rpart);
-                        w[e >> 1] = b0 | (b1 << 16);
+                        for (int e = 0; e < 8; e += 2)
+                            lw[e >> 1] = split_low(v[e] - bf16_lo(hw[e >> 1]), v[e + 1] - bf16_hi(hw[e >> 1]), lpart, rpart);
+                        P16lo.b[p][c] = __builtin_bit_cast(bf16x8, lw);
                     }
-                    u32x4 wv = {w[0], w[1], w[2], w[3]};
-                    P16lo.b[p][c] = __builtin_bit_cast(bf16x8, wv);
+                    nlo[p] = sqrtf(lpart + __shfl_xor(lpart, 32));
+                    nre[p] = sqrtf(rpart + __shfl_xor(rpart, 32));
                 }
-                const float nlo = sqrtf(lpart + __shfl_xor(lpart, 32));
-                const float nr = sqrtf(rpart + __shfl_xor(rpart, 32));
                 const float sx = sqrtf(xnp[p]);
                 const float facc3 = (6.f * DP + 16.f) * U32 * (sx + lmax) * (sx + lmax);
-                e2[p] = 1.01f * (nr * (2.f * lmax + ra) + la * nlo + ra * sx + facc3);
+                e2[p] = 1.01f * (nre[p] * (2.f * lmax + ra) + la * nlo[p] + ra * sx + facc3);
             }
         } else {
             e2[0] = e32[0];
@@ -1265,7 +1434,7 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
             for (int p = 0; p < 2; ++p) {
                 const int64_t si = pbase + 32 * p + i32;
                 const bool valid = si < a.n;
-                const float *xr = a.X + (valid ? slot_point(a, si) : 0) * a.ldx;
+                const float *xr = a.X + (valid ? slot_point<ROWS>(a, si) : 0) * a.ldx;
 #pragma unroll
                 for (int s = 0; s < 8 * DC; ++s) {
                     const int dd = 2 * s + h;
@@ -1310,7 +1479,7 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                     }
                 }
             };
-            if (a.pt_order) {
+            if (ordered) {
                 // tau + E16 + E2, rounded up, as an approximate delta^2
                 unsigned thr16[2];
 #pragma unroll
@@ -1319,10 +1488,7 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                     const float thr = (tau[p] + w) + 4.f * U32 * (fabsf(tau[p]) + w);
                     thr16[p] = (unsigned)max(__float_as_int(thr + xnp[p]), 0) >> 16;
                 }
-                if (a.lds_tiles)
-                    screen_pass2_tiles(BoolTag<true>{}, P32, pass2_consume_skip, pass2_store, thr16);
-                else
-                    screen_pass2_tiles(BoolTag<false>{}, P32, pass2_consume_skip, pass2_store, thr16);
+                if constexpr (ROWS == 0) screen_pass2_tiles(P32, pass2_consume_skip, pass2_store, thr16);
             } else if constexpr (MODE == 1) {
                 if (a.lds_tiles)
                     screen_pass_split(BoolTag<true>{}, pass2_consume, pass2_store);
@@ -1360,7 +1526,7 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
 
         // ---------------- phase B: one lane per point (lane l <-> slot pbase + l)
         const bool valid = pbase + lane < a.n;
-        const int64_t pi = valid ? slot_point(a, pbase + lane) : 0;  // the point's own index
+        const int64_t pi = valid ? slot_point<ROWS>(a, pbase + lane) : 0;  // the point's own index
         const float cert_rhs = certL[lane];
         // The point's row.  ROWS = 1: in the lane's registers.  ROWS = 0 (landmark
         // rows from memory): the four lanes of a quad rescore one candidate at a

@@ -794,6 +794,7 @@ hipError_t launch_main_m0_kp16_kf0(const EmbedArgs &, int, int, size_t, int, hip
 hipError_t launch_main_m0_kp20_kf0(const EmbedArgs &, int, int, size_t, int, hipStream_t);
 hipError_t launch_main_m0_kp20_kf1(const EmbedArgs &, int, int, size_t, int, hipStream_t);
 hipError_t launch_main_m0_kp24_kf0(const EmbedArgs &, int, int, size_t, int, hipStream_t);
+hipError_t launch_main_m0_kp24_kf1(const EmbedArgs &, int, int, size_t, int, hipStream_t);
 hipError_t launch_main_m0_kp32_kf0(const EmbedArgs &, int, int, size_t, int, hipStream_t);
 hipError_t launch_main_m0_kp8_kf1(const EmbedArgs &, int, int, size_t, int, hipStream_t);
 hipError_t launch_main_m0_kp16_kf1(const EmbedArgs &, int, int, size_t, int, hipStream_t);
@@ -803,6 +804,7 @@ hipError_t launch_main_m1_kp16_kf0(const EmbedArgs &, int, int, size_t, int, hip
 hipError_t launch_main_m1_kp20_kf0(const EmbedArgs &, int, int, size_t, int, hipStream_t);
 hipError_t launch_main_m1_kp20_kf1(const EmbedArgs &, int, int, size_t, int, hipStream_t);
 hipError_t launch_main_m1_kp24_kf0(const EmbedArgs &, int, int, size_t, int, hipStream_t);
+hipError_t launch_main_m1_kp24_kf1(const EmbedArgs &, int, int, size_t, int, hipStream_t);
 hipError_t launch_main_m1_kp32_kf0(const EmbedArgs &, int, int, size_t, int, hipStream_t);
 hipError_t launch_main_m1_kp8_kf1(const EmbedArgs &, int, int, size_t, int, hipStream_t);
 hipError_t launch_main_m1_kp16_kf1(const EmbedArgs &, int, int, size_t, int, hipStream_t);
@@ -818,13 +820,15 @@ hipError_t launch_embed(const EmbedArgs &a0, int mode, int kp, int num_cus, size
     // CU: 3 or 2 waves per SIMD, main_max_block) still fits beside them;
     // otherwise rescore from global memory with 4-wave blocks, several per CU.
     // The screen operands (A tiles and norms, read by every wave twice per 64
-    // points) join them in LDS when that still fits.
+    // points) join them in LDS when that still fits.  Points in locality order
+    // share their few rows and tiles through the caches, and only the kernels
+    // without LDS rows carry their screen (the others keep their registers).
     const int max_wpb = main_max_block(mode, dc, kp) / 64;
     int wpb;
     const size_t fixed = CENT_LDS_BYTES + order_lds_bytes(a.g);
     const size_t tiles = tile_lds_bytes(mode, a.ntiles, dc);
     a.lds_tiles = 0;
-    if (fixed + rows + (size_t)max_wpb * wsm <= lds_per_block) {
+    if (!a.pt_order && fixed + rows + (size_t)max_wpb * wsm <= lds_per_block) {
         a.lds_rows = 1;
         wpb = max_wpb;
         if (fixed + rows + tiles + (size_t)max_wpb * wsm <= lds_per_block) a.lds_tiles = 1;
@@ -836,19 +840,19 @@ hipError_t launch_embed(const EmbedArgs &a0, int mode, int kp, int num_cus, size
     }
     const size_t smem = fixed + (a.lds_rows ? rows : 0) + (a.lds_tiles ? tiles : 0) + (size_t)wpb * wsm;
     const int block = 64 * wpb;
-    // k == KP with k < g has its own instantiation (KP 8, 16, 20 and 32)
-    const bool kf = a.k == kp && a.kact == kp - 1 && kp != 24;
+    // k == KP with k < g has its own instantiation
+    const bool kf = a.k == kp && a.kact == kp - 1;
     if (mode == 0) {
         if (kp == 8) return (kf ? launch_main_m0_kp8_kf1 : launch_main_m0_kp8_kf0)(a, dc, block, smem, num_cus, s);
         if (kp == 16) return (kf ? launch_main_m0_kp16_kf1 : launch_main_m0_kp16_kf0)(a, dc, block, smem, num_cus, s);
         if (kp == 20) return (kf ? launch_main_m0_kp20_kf1 : launch_main_m0_kp20_kf0)(a, dc, block, smem, num_cus, s);
-        if (kp == 24) return launch_main_m0_kp24_kf0(a, dc, block, smem, num_cus, s);
+        if (kp == 24) return (kf ? launch_main_m0_kp24_kf1 : launch_main_m0_kp24_kf0)(a, dc, block, smem, num_cus, s);
         return (kf ? launch_main_m0_kp32_kf1 : launch_main_m0_kp32_kf0)(a, dc, block, smem, num_cus, s);
     }
     if (kp == 8) return (kf ? launch_main_m1_kp8_kf1 : launch_main_m1_kp8_kf0)(a, dc, block, smem, num_cus, s);
     if (kp == 16) return (kf ? launch_main_m1_kp16_kf1 : launch_main_m1_kp16_kf0)(a, dc, block, smem, num_cus, s);
     if (kp == 20) return (kf ? launch_main_m1_kp20_kf1 : launch_main_m1_kp20_kf0)(a, dc, block, smem, num_cus, s);
-    if (kp == 24) return launch_main_m1_kp24_kf0(a, dc, block, smem, num_cus, s);
+    if (kp == 24) return (kf ? launch_main_m1_kp24_kf1 : launch_main_m1_kp24_kf0)(a, dc, block, smem, num_cus, s);
     return (kf ? launch_main_m1_kp32_kf1 : launch_main_m1_kp32_kf0)(a, dc, block, smem, num_cus, s);
 }
 

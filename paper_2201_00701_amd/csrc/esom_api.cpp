@@ -40,6 +40,8 @@ struct esom_ctx {
     // 3-D projection: neighbour lists when the caller asks for none
     int32_t *k3idx = nullptr;
     size_t k3idx_bytes = 0;
+    double *k3tab = nullptr;  // and its FP64 pair table
+    size_t k3tab_bytes = 0;
     // graph layout: the other position buffer of the synchronous steps and the
     // nodes' edge lists
     void *lay = nullptr;
@@ -660,6 +662,7 @@ void esom_destroy(esom_ctx *c) {
     dev_free(c, reinterpret_cast<void *&>(c->som_xb), c->som_xb_bytes);
     dev_free(c, reinterpret_cast<void *&>(c->nearest), sizeof(int32_t) * (size_t)c->nearest_cap);
     dev_free(c, reinterpret_cast<void *&>(c->k3idx), c->k3idx_bytes);
+    dev_free(c, reinterpret_cast<void *&>(c->k3tab), c->k3tab_bytes);
     dev_free(c, c->lay, c->lay_bytes);
     dev_free(c, reinterpret_cast<void *&>(c->counters), sizeof(unsigned long long) * C_COUNT);
     if (c->sc.join) (void)hipEventDestroy(c->sc.join);
@@ -959,16 +962,33 @@ int esom_embed3(esom_ctx *c, const float *X, int64_t n, int32_t d, int64_t ldx, 
     st = run_embed(c, X, n, d, ldx, L_hd, nullptr, g, P, nullptr, kidx, nullptr, EMBED_KNN_ONLY, s,
                    nullptr, knn_idx ? 1 : 0);
     if (st != ESOM_OK) return st;
-    Embed3Args a;
+    // the FP64 pair table, where it pays and the budget has room for it
+    size_t tb = embed3_table_bytes(n, g, P.k);
+    if (tb > c->k3tab_bytes && c->budget && c->held - c->k3tab_bytes + tb > c->budget) tb = 0;
+    if (tb > c->k3tab_bytes) {
+        if (c->k3tab) {
+            e = hipStreamSynchronize(s);
+            if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
+            dev_free(c, reinterpret_cast<void *&>(c->k3tab), c->k3tab_bytes);
+            c->k3tab_bytes = 0;
+        }
+        st = dev_alloc(c, reinterpret_cast<void **>(&c->k3tab), tb);
+        if (st != ESOM_OK) return st;
+        c->k3tab_bytes = tb;
+    }
+    ListArgs a;
+    memset(&a, 0, sizeof a);
     a.X = X;
     a.n = n;
     a.ldx = ldx;
     a.d = d;
+    a.dp = c->sc.prep.dp;
     a.g = g;
     a.k = P.k;
     a.use_cutoff = P.k < g ? 1 : 0;
-    a.L = L_hd;
-    a.l3 = L_3d;
+    a.Lpad = c->sc.prep.Lpad;
+    a.ipos = c->sc.prep.ipos;
+    a.l = L_3d;
     a.knn_idx = kidx;
     a.Wk = harmonic(P.k);
     a.boost = P.boost;
@@ -976,7 +996,7 @@ int esom_embed3(esom_ctx *c, const float *X, int64_t n, int32_t d, int64_t ldx, 
     a.gravity = P.gravity;
     a.adjust = P.adjust;
     a.out = out;
-    e = launch_embed3(a, c->num_cus, s);
+    e = launch_embed3(a, tb ? c->k3tab : nullptr, c->num_cus, s);
     if (e != hipSuccess) return hip_fail(e, "3-D projection launch");
     return ESOM_OK;
 }

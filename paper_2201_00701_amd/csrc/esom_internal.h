@@ -197,18 +197,26 @@ struct MatArgs {
 };
 hipError_t launch_materialise(const MatArgs &m, int num_cus, hipStream_t s);
 
-// Projection into 3-D from given k nearest landmarks (esom_embed3.hip).
-struct Embed3Args {
+// Exact projection from given k nearest landmarks (list_project.h).
+struct ListArgs {
     const float *X;
     int64_t n, ldx;
-    int d, g, k, use_cutoff;
-    const float *L, *l3;       // g x d, g x 3
+    int d, dp, g, k, use_cutoff;
+    const float *Lpad;         // padded rows by position
+    const int32_t *ipos;       // landmark -> position
+    const float *l;            // landmark positions, g x M
+    const double *tab;         // g x g: 1 / (2 |L_u - L_v|^2) by position, or NULL
     const int32_t *knn_idx;    // n x k (any order; entries outside [0, g): NaN output)
     double Wk;                 // the k-th harmonic number
     double boost, cutoff, gravity, adjust;
-    float *out;                // n x 3
+    float *out;                // n x M
+    int32_t *out_idx;          // n x k: the sorted list, or NULL
+    float *out_d2;             // n x k: its squared distances, or NULL
 };
-hipError_t launch_embed3(const Embed3Args &e, int num_cus, hipStream_t s);
+// Projection into 3-D (esom_embed3.hip).  tab: embed3_table_bytes of scratch, or
+// NULL (0 bytes wanted, or none to be had): the pairs then read the rows.
+size_t embed3_table_bytes(int64_t n, int g, int k);
+hipError_t launch_embed3(const ListArgs &e, double *tab, int num_cus, hipStream_t s);
 
 // The paper's kernel families as ablations (esom_ablation.hip).
 constexpr int ABL_MAX_K = 64;

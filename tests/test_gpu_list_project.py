@@ -1,0 +1,64 @@
+"""Edges of the FP64 projection from neighbour lists (3-D output): every lane
+group (k on both sides of 16 and 32), with and without the pair table, ragged rows,
+k = g, duplicated landmarks and nearly coincident ones."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_dev():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    return torch
+
+
+# (n, d, g, k, budget): few points for the landmarks or a budget without room
+# take the direct pair projection, the others the table
+@pytest.mark.parametrize("n,d,g,k,tight,adjust", [
+    (1, 3, 3, 3, False, 1.0), (900, 5, 20, 16, False, 1.0), (901, 17, 40, 17, False, 0.5),
+    (2000, 33, 64, 32, False, 1.0), (777, 16, 70, 33, False, 1.0), (1500, 70, 64, 64, False, 1.0),
+    (2000, 20, 60, 12, True, 1.0), (65, 12, 700, 8, False, 1.0), (3000, 31, 50, 50, False, 1.0)])
+def test_embed3_groups(torch_dev, oracle_mod, n, d, g, k, tight, adjust):
+    from paper_2201_00701_amd import esom
+    rng = np.random.default_rng(n + d + k)
+    L = rng.normal(0, 2, (g, d)).astype(np.float32)
+    l3 = rng.normal(0, 3, (g, 3)).astype(np.float32)
+    X = rng.normal(0, 2, (n, d)).astype(np.float32)
+    if g > 10:
+        L[7] = L[3]                            # coincident landmarks
+        L[9] = L[4] * np.float32(1 + 2e-6)     # polarisation loses all digits here
+        l3[5] = l3[6]
+    dev = lambda a: torch_dev.from_numpy(np.ascontiguousarray(a)).cuda()
+    probe = esom.Context(0)
+    ctx = probe
+    try:
+        print("case embed3 groups n=%d d=%d g=%d k=%d tight=%s" % (n, d, g, k, tight), flush=True)
+        if tight:
+            # a budget of what the neighbour search holds, the table of g x g
+            # doubles beyond it (the search's pair table is not allocated)
+            for kb in range(1, 4096, 8):
+                ctx = esom.Context(0, kb << 10)
+                try:
+                    ctx.embed3(dev(X), dev(L), dev(l3), k=k, adjust=adjust)
+                    break
+                except esom.EsomError:
+                    ctx.close()
+        out, idx = ctx.embed3(dev(X), dev(L), dev(l3), k=k, adjust=adjust, knn=True)
+        out, idx = out.cpu().numpy().astype(np.float64), idx.cpu().numpy()
+    finally:
+        ctx.close()
+        probe.close()
+    ref = oracle_mod.embed3(X, L, l3, k, adjust=adjust, threads=8)
+    np.testing.assert_array_equal(np.sort(idx, 1), np.sort(ref["idx"][:, :k], 1))
+    # FP64 on both sides and one rounding to FP32, relative to the output itself (a
+    # nearly coincident pair extrapolates: outputs up to 10^5 times the span, whose
+    # rounding alone exceeds any bound in terms of the span); polarisation at its
+    # limit (10^6) loses 20 of the 53 bits in a pair's coordinate, and a system at
+    # the singularity bound (condition below 4e9) keeps 1e-6 of what is left
+    span = float(np.ptp(l3, axis=0).max())
+    scale = np.maximum(span, np.abs(ref["out"]).max(axis=1))
+    err = np.abs(out - ref["out"]).max(axis=1) / scale
+    assert np.quantile(err, 0.99) <= 2.0 ** -22
+    assert err.max() <= 1e-4

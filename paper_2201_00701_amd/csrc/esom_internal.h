@@ -181,7 +181,6 @@ hipError_t launch_update(const UpdateArgs &u, void *ws, bool tight, hipStream_t 
 
 // The materialised-distance path (esom_materialise.hip): keys of a chunk of
 // points in device memory, then selection, exact rescoring and certificate.
-constexpr int MAT_MAX_C = 40;                    // candidates per point (k + 2, k <= 32)
 constexpr size_t MAT_KEY_BYTES = (size_t)256 << 20;  // keys of one chunk at most
 struct MatArgs {
     const float *X;      // the chunk's rows (stride ldx)
@@ -190,7 +189,7 @@ struct MatArgs {
     const void *A;       // FP32 MFMA operand of the preparation (tile layout)
     const float *norms, *cent, *Lpad, *lmax;
     const int32_t *perm; // position -> landmark
-    float *keys;         // n x gpad
+    float *keys;         // n x gpad, in the order of key_position
     int32_t *knn_idx;    // n x k
     float *knn_d2;       // n x k
     uint8_t *knn_mark;   // n: 1 = the exact path decides this point

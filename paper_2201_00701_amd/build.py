@@ -26,6 +26,7 @@ UNITS = [("esom_core.hip", []), ("esom_update.hip", []), ("esom_api.cpp", ["-x",
          ("esom_serve.cpp", ["-x", "hip"]), ("esom_som.hip", []), ("esom_graph.hip", []),
          ("esom_embed3.hip", []), ("esom_ablation.hip", []),
          ("esom_materialise.hip", []), ("esom_bin.hip", [])]
+UNITS.append(("embed_inst.hip", ["-DINST_MODE=1", "-DINST_KP=1", "-DINST_KF=1"]))
 for mode in (0, 1):
     for kp in (8, 16, 20, 24, 32):
         UNITS.append(("embed_inst.hip", ["-DINST_MODE=%d" % mode, "-DINST_KP=%d" % kp, "-DINST_KF=0"]))

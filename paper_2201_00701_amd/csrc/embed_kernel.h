@@ -386,16 +386,18 @@ template <int A, int B, class F>
 __device__ __forceinline__ void static_for(F &&f);
 
 // Insert v into the ascending list s; whatever falls off the end updates rej
-// (the smallest key ever rejected).
+// (the smallest key ever rejected).  Every slot becomes min(s[q], max(s[q - 1],
+// v)) of the old values, from the end on in place: the same two operations a slot
+// as carrying the displaced value along, without its chain of KP maxima.
 template <int KP>
 __device__ __forceinline__ void insert_sorted(double (&s)[KP], double &rej, double v) {
+    rej = vmin64(rej, vmax64(s[KP - 1], v));
 #pragma unroll
-    for (int q = 0; q < KP; ++q) {
-        const double hi = vmax64(s[q], v);
-        asm("v_min_f64 %0, %0, %1" : "+v"(s[q]) : "v"(v));  // in place: no copies of the list
-        v = hi;
+    for (int q = KP - 1; q > 0; --q) {
+        const double t = vmax64(s[q - 1], v);
+        asm("v_min_f64 %0, %0, %1" : "+v"(s[q]) : "v"(t));  // in place: no copies of the list
     }
-    rej = vmin64(rej, v);
+    asm("v_min_f64 %0, %0, %1" : "+v"(s[0]) : "v"(v));
 }
 
 // Next non-empty 64-bit bitmap word of a point: mk marks the non-empty words
@@ -431,6 +433,10 @@ __device__ __forceinline__ void static_for(F &&f) {
 // stride of 20 floats free of bank conflicts for 16-byte reads.
 constexpr int PAIR_STRIDE = 20;
 constexpr int PAIR_LDS_BYTES = 64 * PAIR_STRIDE * 4;
+// LDS of the split operand's low parts of a wave's 64 points (padded dimension
+// <= 32).
+constexpr int SPLIT_LDS_BYTES = 64 * 32 * 2;
+static_assert(SPLIT_LDS_BYTES <= PAIR_LDS_BYTES, "one region");
 
 // LDS bytes of the block-wide centroid copy (padded dimension <= 128).
 constexpr int CENT_LDS_BYTES = 512;
@@ -456,8 +462,10 @@ __host__ __device__ inline int wave_smem_bytes(int kp, int k, int npair_tiles) {
     const int bits = 2 * npair_tiles * 64 * 4;
     const int nbr = kp > 24 ? k * 64 * 10 : 0;
     const int all = (bits > nbr ? bits : nbr) + 512 + 1024;
-    // (kp = 16: the pair loop's rows, once the rest is done with)
-    return kp == 16 && all < PAIR_LDS_BYTES ? PAIR_LDS_BYTES : all;
+    // (kp = 16: the pair loop's rows, once the rest is done with; up to 16 the
+    // split operand's low parts before the rest is written)
+    const int least = kp == 16 ? PAIR_LDS_BYTES : kp < 16 ? SPLIT_LDS_BYTES : 0;
+    return all < least ? least : all;
 }
 
 // Centred values x_t - c_t of dimensions 16 c + 8 h + e (e < 8) of the point
@@ -964,6 +972,22 @@ __device__ __forceinline__ unsigned project_point(const EmbedArgs &a, const doub
     return reason;
 }
 
+// Lists a point for the exact path, from the front, or (order alone open) for
+// embed_reorder, from the back.
+__device__ __forceinline__ void list_point(const EmbedArgs &a, int64_t pi, unsigned reason, float thr) {
+    if (reason == R_ORDER && a.order_list) {
+        const int64_t slot = a.fb_cap - 1 - (int64_t)atomicAdd(&a.counters[C_ORD_LEN], 1ull);
+        a.fb_list[slot] = (int32_t)pi;
+        a.fb_reason[slot] = (uint8_t)R_NEARTIE;
+        return;
+    }
+    if (reason & R_ORDER) reason = (reason & ~(unsigned)R_ORDER) | R_NEARTIE;
+    const unsigned long long slot = atomicAdd(&a.counters[C_FB_LEN], 1ull);
+    a.fb_list[slot] = (int32_t)pi;
+    a.fb_reason[slot] = (uint8_t)reason;
+    a.fb_thresh[slot] = thr;
+}
+
 // Projection only (phases of scores, pairs and solve) from given k nearest
 // landmarks (knn_idx / knn_d2, sorted by (distance, index)), e.g. cached from
 // an earlier call with the same high-dimensional landmarks.
@@ -1004,7 +1028,8 @@ __global__ void __launch_bounds__(256) embed_project(EmbedArgs a) {
                 sk[q] = pack_key(a.knn_d2[pi * a.k + q], j);
             }
         }
-        unsigned reason = (valid && a.knn_mark && a.knn_mark[pi]) ? (unsigned)R_NEARTIE : 0u;
+        const unsigned mark = valid && a.knn_mark ? a.knn_mark[pi] : 0u;
+        unsigned reason = mark == 0u ? 0u : mark == 2u ? (unsigned)R_ORDER : (unsigned)R_NEARTIE;
         if (bad_idx) reason |= R_UNCERT;
         float d2k = INFINITY;
 #pragma unroll
@@ -1025,12 +1050,7 @@ __global__ void __launch_bounds__(256) embed_project(EmbedArgs a) {
         int nref = 0;
         if constexpr (KP <= 8) reason |= refine_cutoffs<KP>(a, sk, valid, d2x, cref, nref);
         reason = project_point<KP>(a, sk, lane, valid, pi, reason, nbD2, nbS, nbI, iposL, cref, nref);
-        if (valid && reason) {
-            const unsigned long long slot = atomicAdd(&a.counters[C_FB_LEN], 1ull);
-            a.fb_list[slot] = (int32_t)pi;
-            a.fb_reason[slot] = (uint8_t)reason;
-            a.fb_thresh[slot] = thr;
-        }
+        if (valid && reason) list_point(a, pi, reason, thr);
     }
 }
 
@@ -1040,6 +1060,9 @@ __global__ void __launch_bounds__(256) embed_project(EmbedArgs a) {
 // KF = 1: k == KP and k < g (so k - 1 neighbours are active), known at
 // compile time: the loops over the sorted list and the pairs lose their
 // bounds tests (5% faster at 1M x 32-D with k = 16, 4% at 10M x 64-D).
+// KP = 1 (KF = 1 only): the nearest landmark of the landmark update, with no
+// projection.  1M x 32-D, 400 landmarks: 460 us with the 8-entry list of the k <=
+// 8 kernel in FP32 mode, now 150 us.
 template <int MODE, int DC, int KP, int ROWS, int KF>
 __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(EmbedArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1121,9 +1144,14 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
         float nlo[2], nre[2];  // BF16 mode: |lo| and |r| of the split (see e2)
         // Low parts of two split values from their remainders after the high
         // parts, adding to |lo|^2 and |r|^2.  BF16 mode forms them with the high
-        // parts where the registers allow holding them through pass 1 (the
-        // 12-wave blocks' do not: they read the rows again).
-        constexpr bool SPLIT_EARLY = MODE == 1 && main_max_block(MODE, DC, KP) == 512 && DC <= 4;
+        // parts and holds them through pass 1 in registers, or where 12 waves
+        // leave none in the wave's LDS, which pass 2 writes afterwards (not with
+        // points in locality order, whose pass 1 uses it, nor beyond 64 padded
+        // dimensions: there the rows are read again; at 1M x 32-D that took 11K of
+        // the tile's 112K cycles).
+        constexpr bool SPLIT_STASH = MODE == 1 && main_max_block(MODE, DC, KP) == 768 && ROWS == 1;
+        constexpr bool SPLIT_EARLY = SPLIT_STASH || (MODE == 1 && main_max_block(MODE, DC, KP) == 512 && DC <= 4);
+        u32x4 *stash = reinterpret_cast<u32x4 *>(wsm) + lane;
         auto split_low = [](float r0, float r1, float &lsum, float &rsum) -> unsigned {
             const unsigned lw = bf16_pair(r0, r1);
             const float l0 = bf16_lo(lw), l1 = bf16_hi(lw);
@@ -1157,7 +1185,10 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                     if constexpr (SPLIT_EARLY) lw[e >> 1] = split_low(q0, q1, lpart, rpart);
                 }
                 P16.b[p][c] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
-                if constexpr (SPLIT_EARLY) P16lo.b[p][c] = __builtin_bit_cast(bf16x8, u32x4{lw[0], lw[1], lw[2], lw[3]});
+                if constexpr (SPLIT_STASH)
+                    stash[(p * DC + c) * 64] = u32x4{lw[0], lw[1], lw[2], lw[3]};
+                else if constexpr (SPLIT_EARLY)
+                    P16lo.b[p][c] = __builtin_bit_cast(bf16x8, u32x4{lw[0], lw[1], lw[2], lw[3]});
             }
             xnp[p] = part + __shfl_xor(part, 32);
             dxp[p] = dpart + __shfl_xor(dpart, 32);
@@ -1225,14 +1256,18 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
         auto screen_pass_split = [&](auto in_lds, auto consume, auto store) {
             const void *Ab = decltype(in_lds)::value ? static_cast<const void *>(tilesL) : a.A;
             const float *Nb = decltype(in_lds)::value ? normsL : a.norms;
-            TileRegs<1, DC> Th, Tl;
+            // the low parts one tile ahead (their latency took 8K cycles a wave at
+            // 1M x 32-D, where the high parts are in LDS)
+            TileRegs<1, DC> Th, Tl[2];
+            load_tile<1, DC>(a.A16, 0, lane, Tl[0]);
             for (int tp = 0; tp < W; ++tp) {
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
+                    const int t = 2 * tp + half;
                     f32x16 acc[2];
-                    load_tile<1, DC>(Ab, 2 * tp + half, lane, Th);
-                    load_tile<1, DC>(a.A16, 2 * tp + half, lane, Tl);
-                    screen_tile_split<DC>(Nb, 2 * tp + half, lane, Th, Tl, P16, P16lo, acc);
+                    load_tile<1, DC>(a.A16, t + 1 < 2 * W ? t + 1 : t, lane, Tl[1 - half]);
+                    load_tile<1, DC>(Ab, t, lane, Th);
+                    screen_tile_split<DC>(Nb, t, lane, Th, Tl[half], P16, P16lo, acc);
                     consume(acc, half);
                 }
                 store(tp);
@@ -1364,8 +1399,13 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                 v1[r] = max(__float_as_int(gmin[p][1][r] + xnp[p]), 0);
             }
             // (k known at compile time and C = k, the default)
-            constexpr bool STATIC_J = KF == 1 && KP <= 24;
-            if (STATIC_J && a.pair_select && a.jsel == KP) {
+            constexpr bool STATIC_J = KF == 1 && KP >= 8 && KP <= 24;
+            if constexpr (KP == 1) {
+                int t = v0[0];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) t = min(t, min(v0[r], v1[r]));
+                tbase[p] = __int_as_float(min(min(t, __shfl_xor(t, 32)), 0x7F7FFFFF));
+            } else if (STATIC_J && a.pair_select && a.jsel == KP) {
                 if constexpr (STATIC_J) tbase[p] = __int_as_float(min(select_pair_static<KP>(v0, v1), 0x7F7FFFFF));
             } else if (a.pair_select) {
                 const int tl = min(select_pair_jth(v0, v1, a.jsel), 0x7F7FFFFF);  // +inf -> FLT_MAX
@@ -1441,6 +1481,14 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                     P32.b[p][s] = (valid && dd < a.d) ? xr[dd] - centL[dd] : 0.f;
                 }
             }
+        }
+
+        if constexpr (SPLIT_STASH) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int c = 0; c < DC; ++c) P16lo.b[p][c] = __builtin_bit_cast(bf16x8, stash[(p * DC + c) * 64]);
+            wave_lds_fence();
         }
 
         // ---------------- pass 2: candidate bitmaps (key <= tau) into LDS.  The
@@ -1680,15 +1728,15 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
             if (m > a.k && d2k1 - d2k <= 2.f * (DP + 3) * U32 * d2k1) reason |= R_NEARTIE;
             // When the caller asked for the neighbour list (its first entry is the
             // nearest landmark of the landmark update), adjacent entries closer
-            // than the rounding bound go to the exact path too, so the list is
-            // ordered by exact distance.  (The serving cache keeps the fast
-            // path's own order, which is what a fresh projection uses.)
+            // than the rounding bound are ranked again, so the list is ordered
+            // by exact distance.  (The serving cache keeps the fast path's own
+            // order, which is what a fresh projection uses.)
             if (a.knn_exact_order) {
                 float prev = key_d2(sk[0]);
 #pragma unroll
                 for (int q = 1; q < KP; ++q) {
                     const float cur = key_d2(sk[q]);
-                    if (q < a.k && q < m && cur - prev <= 2.f * (DP + 3) * U32 * cur) reason |= R_NEARTIE;
+                    if (q < a.k && q < m && cur - prev <= 2.f * (DP + 3) * U32 * cur) reason |= R_ORDER;
                     prev = cur;
                 }
             }
@@ -1704,7 +1752,7 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
         // alone cost 8% of this kernel (register pressure), used or not.
         float cref[N_REFINE] = {};
         int nref = 0;
-        if constexpr (KP <= 8) {
+        if constexpr (KP <= 8 && KP > 1) {
             if (!a.knn_only) {
                 // rows of more than 64 dimensions, or held by quads, are read
                 // again from memory
@@ -1761,16 +1809,11 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
             }
         }
 
-        if (!a.knn_only) {
+        if (KP > 1 && !a.knn_only) {
             __builtin_amdgcn_wave_barrier();
-            reason = project_point<KP>(a, sk, lane, valid, pi, reason, nbD2, nbS, nbI, iposL, cref, nref);
+            if constexpr (KP > 1) reason = project_point<KP>(a, sk, lane, valid, pi, reason, nbD2, nbS, nbI, iposL, cref, nref);
         }
-        if (valid && reason) {
-            const unsigned long long slot = atomicAdd(&a.counters[C_FB_LEN], 1ull);
-            a.fb_list[slot] = (int32_t)pi;
-            a.fb_reason[slot] = (uint8_t)reason;
-            a.fb_thresh[slot] = thr;
-        }
+        if (valid && reason) list_point(a, pi, reason, thr);
         st_cand += valid ? (unsigned long long)m : 0ull;
     }
     // wave-level totals

@@ -119,6 +119,7 @@ size_t carve(Scratch &sc, void *base, int64_t n, int g, int dp, int pg, int64_t 
     sc.prep.pcl = static_cast<int32_t *>(take(sizeof(int32_t) * (size_t)g));
     sc.prep.pdist = static_cast<float *>(take(sizeof(float) * (size_t)g));
     sc.prep.ppiv = static_cast<float *>(take(sizeof(float) * 64 * 64));
+    sc.fb_cap = n > 0 ? n : 1;
     sc.fb_list = static_cast<int32_t *>(take(sizeof(int32_t) * (size_t)(n > 0 ? n : 1)));
     sc.fb_reason = static_cast<uint8_t *>(take((size_t)(n > 0 ? n : 1)));
     sc.fb_thresh = static_cast<float *>(take(sizeof(float) * (size_t)(n > 0 ? n : 1)));
@@ -206,7 +207,8 @@ Plan make_plan(int d, int g, int k, int mode, int candidates) {
     Plan p;
     p.dp = 16 * ((d + 15) / 16);
     p.dc = p.dp / 16;
-    p.kp = k <= 8 ? 8 : k <= 16 ? 16 : k <= 20 ? 20 : k <= 24 ? 24 : k <= 32 ? 32 : 0;
+    // (k = 1: the nearest landmark, wanted in BF16 mode only)
+    p.kp = k == 1 && mode == 1 ? 1 : k <= 8 ? 8 : k <= 16 ? 16 : k <= 20 ? 20 : k <= 24 ? 24 : k <= 32 ? 32 : 0;
     const int maxdc = mode == 1 ? FAST_MAX_DC_BF16 : FAST_MAX_DC_FP32;
     p.fast = p.kp != 0 && p.dc <= maxdc && g <= FAST_MAX_G;
     p.mat = !p.fast && p.kp != 0 && g <= FAST_MAX_G && p.dp <= ESOM_MAX_D;
@@ -339,10 +341,12 @@ int enqueue_embed(Scratch &sc, unsigned long long *counters, int num_cus, size_t
     a.Wk = (float)harmonic(P.k);
     a.fb_list = sc.fb_list;
     a.fb_reason = sc.fb_reason;
+    a.fb_cap = sc.fb_cap;
     a.fb_thresh = sc.fb_thresh;
     a.counters = counters;
     a.knn_only = knn_only;
-    a.knn_exact_order = (exact_order && knn_idx) ? 1 : 0;
+    // (a list without a projection is ranked by who reads it)
+    a.knn_exact_order = (exact_order && knn_idx && what == EMBED_FULL) ? 1 : 0;
     // Points go in chunks of at most `chunk` (the fallback list's capacity):
     // each chunk is screened, then its listed points are recomputed, before
     // the next chunk reuses the list.
@@ -360,6 +364,7 @@ int enqueue_embed(Scratch &sc, unsigned long long *counters, int num_cus, size_t
         a.knn_mark = knn_mark ? knn_mark + c0 : nullptr;
         a.x_vec4 = (d == pl.dp && ldx % 4 == 0 && ((uintptr_t)a.X & 15) == 0 &&
                     ((uintptr_t)pr.cent & 15) == 0) ? 1 : 0;
+        a.order_list = a.knn_exact_order && m >= ORDER_MIN_N ? 1 : 0;
         const bool last = c0 + m >= n;
         if (what == EMBED_PROJECT && pl.kp != 0) {
             e = launch_project(a, pl.kp, num_cus, s);
@@ -401,6 +406,7 @@ int enqueue_embed(Scratch &sc, unsigned long long *counters, int num_cus, size_t
             if (e != hipSuccess) return hip_fail(e, "projection kernel launch");
             if (ev && last) (void)hipEventRecord(ev[2], s);
             e = launch_fallback(ap, num_cus, lds_per_block, s);
+            if (e == hipSuccess && ap.order_list) e = launch_reorder(ap, num_cus, s);
             if (e != hipSuccess) return hip_fail(e, "exact-path launch");
         } else if (pl.fast) {
             a.pt_order = nullptr;
@@ -421,6 +427,7 @@ int enqueue_embed(Scratch &sc, unsigned long long *counters, int num_cus, size_t
             if (e != hipSuccess) return hip_fail(e, "embed kernel launch");
             if (ev && last) (void)hipEventRecord(ev[2], s);
             e = launch_fallback(a, num_cus, lds_per_block, s);
+            if (e == hipSuccess && a.order_list) e = launch_reorder(a, num_cus, s);
             if (e != hipSuccess) return hip_fail(e, "exact-path launch");
         } else {
             if (ev && last) (void)hipEventRecord(ev[2], s);
@@ -626,20 +633,27 @@ int esom_get_fallback(esom_ctx *c, void *stream, int32_t *points, uint8_t *reaso
     if (cap < 0) return fail(ESOM_EINVAL, "cap = %lld < 0", (long long)cap);
     int st = esom_sync(c, stream);
     if (st != ESOM_OK) return st;
-    unsigned long long len = 0;
-    hipError_t e = hipMemcpy(&len, c->counters + C_FB_LEN, sizeof len, hipMemcpyDeviceToHost);
+    // the list's front, then the points listed from its end
+    unsigned long long len[2] = {0, 0};
+    static_assert(C_FB_LEN == 0 && C_ORD_LEN == 1, "the two lengths lead the counters");
+    hipError_t e = hipMemcpy(len, c->counters, sizeof len, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
-    if (!c->arena) len = 0;
-    if (len > (unsigned long long)c->cap_n) len = (unsigned long long)c->cap_n;
-    *count = (int64_t)len;
-    const size_t m = (size_t)((int64_t)len < cap ? (int64_t)len : cap);
-    if (m && points) {
-        e = hipMemcpy(points, c->sc.fb_list, m * sizeof(int32_t), hipMemcpyDeviceToHost);
-        if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
-    }
-    if (m && reasons) {
-        e = hipMemcpy(reasons, c->sc.fb_reason, m, hipMemcpyDeviceToHost);
-        if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
+    const int64_t room = c->arena ? c->sc.fb_cap : 0;
+    const int64_t nf = (int64_t)len[0] < room ? (int64_t)len[0] : room;
+    const int64_t no = (int64_t)len[1] < room - nf ? (int64_t)len[1] : room - nf;
+    *count = nf + no;
+    const int64_t m[2] = {nf < cap ? nf : cap, no < cap - (nf < cap ? nf : cap) ? no : cap - (nf < cap ? nf : cap)};
+    const int64_t from[2] = {0, room - no}, to[2] = {0, m[0]};
+    for (int i = 0; i < 2; ++i) {
+        if (m[i] <= 0) continue;
+        if (points) {
+            e = hipMemcpy(points + to[i], c->sc.fb_list + from[i], (size_t)m[i] * sizeof(int32_t), hipMemcpyDeviceToHost);
+            if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
+        }
+        if (reasons) {
+            e = hipMemcpy(reasons + to[i], c->sc.fb_reason + from[i], (size_t)m[i], hipMemcpyDeviceToHost);
+            if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
+        }
     }
     return ESOM_OK;
 }
@@ -809,7 +823,7 @@ int esom_som_train(esom_ctx *c, const float *X, int64_t n, int32_t d, int64_t ld
     esom_params P;
     esom_default_params(&P);
     P.k = 1;
-    P.mode = ESOM_MODE_FP32;
+    P.mode = ESOM_MODE_BF16_RESCORE;
     for (int t = 0; t < steps; ++t) {
         const int32_t *rows = batch_idx + (size_t)t * batch;
         e = launch_som_gather(X, n, ldx, d, rows, batch, c->som_xb, s);
@@ -898,7 +912,7 @@ int esom_landmark_update(esom_ctx *c, const float *X, int64_t n, int32_t d, int6
         esom_params P;
         esom_default_params(&P);
         P.k = 1;
-        P.mode = ESOM_MODE_FP32;
+        P.mode = ESOM_MODE_BF16_RESCORE;
         st = run_embed(c, X, n, d, ldx, L_hd, L_2d, g, P, nullptr, c->nearest, nullptr, EMBED_KNN_ONLY, s);
         if (st != ESOM_OK) return st;
         near = c->nearest;
@@ -959,8 +973,7 @@ int esom_embed3(esom_ctx *c, const float *X, int64_t n, int32_t d, int64_t ldx, 
         kidx = c->k3idx;
     }
     // the k nearest landmarks (screen, exact selection, exact path)
-    st = run_embed(c, X, n, d, ldx, L_hd, nullptr, g, P, nullptr, kidx, nullptr, EMBED_KNN_ONLY, s,
-                   nullptr, knn_idx ? 1 : 0);
+    st = run_embed(c, X, n, d, ldx, L_hd, nullptr, g, P, nullptr, kidx, nullptr, EMBED_KNN_ONLY, s);
     if (st != ESOM_OK) return st;
     // the FP64 pair table, where it pays and the budget has room for it
     size_t tb = embed3_table_bytes(n, g, P.k);
@@ -996,6 +1009,7 @@ int esom_embed3(esom_ctx *c, const float *X, int64_t n, int32_t d, int64_t ldx, 
     a.gravity = P.gravity;
     a.adjust = P.adjust;
     a.out = out;
+    a.out_idx = knn_idx;  // ranked by exact distance
     e = launch_embed3(a, tb ? c->k3tab : nullptr, c->num_cus, s);
     if (e != hipSuccess) return hip_fail(e, "3-D projection launch");
     return ESOM_OK;

@@ -94,6 +94,7 @@ __global__ void prep_centroid(const float *__restrict__ L, int g, int d, int dp,
         lmax[2] = 0.f;
         lmax[3] = 0.f;
         counters[C_FB_LEN] = 0ull;
+        counters[C_ORD_LEN] = 0ull;
         counters[C_POINTS] += (unsigned long long)n_points;
     }
 }
@@ -755,7 +756,7 @@ hipError_t launch_all_to_fallback(const EmbedArgs &a, int num_cus, size_t lds_pe
 }
 
 __global__ void reset_fallback(unsigned long long *counters) {
-    if (threadIdx.x == 0) counters[C_FB_LEN] = 0ull;
+    if (threadIdx.x == 0) counters[C_FB_LEN] = counters[C_ORD_LEN] = 0ull;
 }
 
 hipError_t launch_reset_fallback(unsigned long long *counters, hipStream_t s) {
@@ -799,6 +800,7 @@ hipError_t launch_main_m0_kp32_kf0(const EmbedArgs &, int, int, size_t, int, hip
 hipError_t launch_main_m0_kp8_kf1(const EmbedArgs &, int, int, size_t, int, hipStream_t);
 hipError_t launch_main_m0_kp16_kf1(const EmbedArgs &, int, int, size_t, int, hipStream_t);
 hipError_t launch_main_m0_kp32_kf1(const EmbedArgs &, int, int, size_t, int, hipStream_t);
+hipError_t launch_main_m1_kp1_kf1(const EmbedArgs &, int, int, size_t, int, hipStream_t);
 hipError_t launch_main_m1_kp8_kf0(const EmbedArgs &, int, int, size_t, int, hipStream_t);
 hipError_t launch_main_m1_kp16_kf0(const EmbedArgs &, int, int, size_t, int, hipStream_t);
 hipError_t launch_main_m1_kp20_kf0(const EmbedArgs &, int, int, size_t, int, hipStream_t);
@@ -849,6 +851,7 @@ hipError_t launch_embed(const EmbedArgs &a0, int mode, int kp, int num_cus, size
         if (kp == 24) return (kf ? launch_main_m0_kp24_kf1 : launch_main_m0_kp24_kf0)(a, dc, block, smem, num_cus, s);
         return (kf ? launch_main_m0_kp32_kf1 : launch_main_m0_kp32_kf0)(a, dc, block, smem, num_cus, s);
     }
+    if (kp == 1) return launch_main_m1_kp1_kf1(a, dc, block, smem, num_cus, s);
     if (kp == 8) return (kf ? launch_main_m1_kp8_kf1 : launch_main_m1_kp8_kf0)(a, dc, block, smem, num_cus, s);
     if (kp == 16) return (kf ? launch_main_m1_kp16_kf1 : launch_main_m1_kp16_kf0)(a, dc, block, smem, num_cus, s);
     if (kp == 20) return (kf ? launch_main_m1_kp20_kf1 : launch_main_m1_kp20_kf0)(a, dc, block, smem, num_cus, s);

@@ -21,19 +21,23 @@ constexpr int FAST_MAX_G = 4096;
 // Counter slots (uint64) in the context's device counter array.
 enum Counter {
     C_FB_LEN = 0,    // length of this call's fallback list (reset per call)
-    C_POINTS = 1,
-    C_FALLBACK = 2,
-    C_UNCERT = 3,
-    C_NEARTIE = 4,
-    C_ILLCOND = 5,
-    C_DEGEN = 6,
-    C_CAND = 7,
-    C_SLOW = 8,
+    C_ORD_LEN = 1,   // points listed from its other end, for their order alone (reset per call)
+    C_POINTS = 2,
+    C_FALLBACK = 3,
+    C_UNCERT = 4,
+    C_NEARTIE = 5,
+    C_ILLCOND = 6,
+    C_DEGEN = 7,
+    C_CAND = 8,
+    C_SLOW = 9,
     C_COUNT = 16,
 };
 
-// Fallback reasons (bit flags; a point may carry several).
-enum Reason { R_UNCERT = 1, R_NEARTIE = 2, R_ILLCOND = 4, R_DEGEN = 8 };
+// Fallback reasons (bit flags; a point may carry several).  R_ORDER: adjacent
+// neighbours FP32 cannot order, in a call that returns the list; the set of
+// neighbours is certain.  Points with no other reason are listed from the end of
+// the fallback arrays (as near ties) and only their lists are ranked again.
+enum Reason { R_UNCERT = 1, R_NEARTIE = 2, R_ILLCOND = 4, R_DEGEN = 8, R_ORDER = 16 };
 
 // Prepared landmark set (device buffers owned by a scratch set).
 struct Prep {
@@ -64,6 +68,7 @@ struct Scratch {
     size_t cap_bytes = 0;
     void *base = nullptr;
     int64_t cap_n = 0;
+    int64_t fb_cap = 0;             // entries of the fallback arrays
     int32_t *fb_list = nullptr;     // fallback point list (cap_n)
     uint8_t *fb_reason = nullptr;   // per listed point reason flags (cap_n)
     float *fb_thresh = nullptr;     // per listed point: bound of its k-th distance^2 (cap_n)
@@ -105,6 +110,8 @@ struct EmbedArgs {
     float *knn_d2;
     int32_t *fb_list;
     uint8_t *fb_reason;
+    int64_t fb_cap;  // entries of the fallback arrays (>= n)
+    int order_list;  // 1: points whose list is open in its order alone are listed apart
     // Per listed point, an upper bound of the exact k-th nearest squared
     // distance (from the fast kernel's rescored k-th, widened by its rounding
     // bound), or +inf: the exact path only sorts landmarks within it.
@@ -118,6 +125,7 @@ struct EmbedArgs {
     // point's neighbours came from the exact path because of the screen
     // (uncertified or near tie); a projection from cached neighbours sends
     // such points to the exact path again.
+    // (2, within the wide-data path: only the order of the list is open.)
     uint8_t *knn_mark;
     // 1: adjacent neighbours FP32 cannot order go to the exact path, so that
     // knn_idx is sorted by exact distance (public calls that return the list)
@@ -154,6 +162,13 @@ hipError_t launch_prep(const Prep &P, const float *L, int mode, unsigned long lo
 hipError_t launch_embed(const EmbedArgs &a, int mode, int kp, int num_cus, size_t lds_per_block,
                         hipStream_t s);
 hipError_t launch_fallback(const EmbedArgs &a, int num_cus, size_t lds_per_block, hipStream_t s);
+// Calls of at least this many points rank the lists of points whose order alone
+// is open in a kernel of their own; below, the one launch of the exact path takes
+// them along (20k x 32-D: 140 us a frame against 161).
+constexpr int64_t ORDER_MIN_N = 65536;
+// Ranks the lists of the points listed for their order and projects them again
+// (esom_embed3.hip).
+hipError_t launch_reorder(const EmbedArgs &a, int num_cus, hipStream_t s);
 hipError_t launch_project(const EmbedArgs &a, int kp, int num_cus, hipStream_t s);
 hipError_t launch_all_to_fallback(const EmbedArgs &a, int num_cus, size_t lds_per_block, hipStream_t s);
 // Resets the fallback-list length (counters[C_FB_LEN]) with a one-thread kernel.
@@ -192,7 +207,7 @@ struct MatArgs {
     float *keys;         // n x gpad, in the order of key_position
     int32_t *knn_idx;    // n x k
     float *knn_d2;       // n x k
-    uint8_t *knn_mark;   // n: 1 = the exact path decides this point
+    uint8_t *knn_mark;   // n: 1 = the exact path decides this point, 2 = only the order is open
 };
 hipError_t launch_materialise(const MatArgs &m, int num_cus, hipStream_t s);
 

@@ -224,15 +224,16 @@ __global__ void __launch_bounds__(256) select_kernel(MatArgs m) {
         bool mark = over || !(cnt < m.g ? d2k * (1.f + rb) < rhs : d2k < INFINITY);
         if (d2k1 < INFINITY && d2k1 - d2k <= 2.f * rb * d2k1) mark = true;  // k-th / (k+1)-th closer than FP32 orders
         // adjacent entries FP32 cannot order when the caller wants the exact order
+        bool order = false;
         if (m.exact_order) {
             const float prev = __shfl_up(d2r, 1);
-            if (__ballot(lane > 0 && lane < k && d2r - prev <= 2.f * rb * d2r) != 0ull) mark = true;
+            order = __ballot(lane > 0 && lane < k && d2r - prev <= 2.f * rb * d2r) != 0ull;
         }
         if (lane < k) {
             m.knn_idx[pi * k + lane] = cj[wv][lane];
             m.knn_d2[pi * k + lane] = d2r;
         }
-        if (lane == 0) m.knn_mark[pi] = mark ? 1 : 0;
+        if (lane == 0) m.knn_mark[pi] = mark ? 1 : order ? 2 : 0;
         __builtin_amdgcn_wave_barrier();
     }
 }

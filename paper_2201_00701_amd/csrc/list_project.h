@@ -88,20 +88,50 @@ __device__ __forceinline__ double lp_det3(double a00, double a01, double a02, do
     return a00 * (a11 * a22 - a12 * a21) - a01 * (a10 * a22 - a12 * a20) + a02 * (a10 * a21 - a11 * a20);
 }
 
+// Values t0 .. t0 + 15 of a row of d floats (4-byte aligned), 0 past its end.
+struct __attribute__((packed, aligned(4))) LpFloat4 {
+    float x, y, z, w;
+};
+__device__ __forceinline__ void lp_load16(const float *x, int t0, int d, float (&v)[16]) {
+    if (t0 + 16 <= d) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const LpFloat4 f = *reinterpret_cast<const LpFloat4 *>(x + t0 + 4 * q);
+            v[4 * q] = f.x;
+            v[4 * q + 1] = f.y;
+            v[4 * q + 2] = f.z;
+            v[4 * q + 3] = f.w;
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < 16; ++t) v[t] = t0 + t < d ? x[t0 + t] : 0.f;
+    }
+}
+
 // <x - L_u, H> and |H|^2 of the rows at positions u, v (H = L_v - L_u).
 __device__ __forceinline__ void lp_direct(const ListArgs &e, const float *x, unsigned u, unsigned v, double &xH,
                                           double &HH) {
     const float4 *Lu = reinterpret_cast<const float4 *>(e.Lpad + (size_t)u * e.dp);
     const float4 *Lv = reinterpret_cast<const float4 *>(e.Lpad + (size_t)v * e.dp);
     xH = HH = 0.0;
-    for (int q = 0; q < e.dp / 4; ++q) {
-        const float4 lu = Lu[q], lv = Lv[q];
-        const float a[4] = {lu.x, lu.y, lu.z, lu.w}, b[4] = {lv.x, lv.y, lv.z, lv.w};
+    for (int c = 0; c < e.dp / 16; ++c) {  // 16 dimensions' loads in flight
+        float4 lu[4], lv[4];
+        float xv[16];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const double H = (double)b[t] - (double)a[t];
-            HH = fma(H, H, HH);
-            if (4 * q + t < e.d) xH = fma((double)x[4 * q + t] - (double)a[t], H, xH);
+        for (int q = 0; q < 4; ++q) {
+            lu[q] = Lu[4 * c + q];
+            lv[q] = Lv[4 * c + q];
+        }
+        lp_load16(x, 16 * c, e.d, xv);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float a[4] = {lu[q].x, lu[q].y, lu[q].z, lu[q].w}, b[4] = {lv[q].x, lv[q].y, lv[q].z, lv[q].w};
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const double H = (double)b[t] - (double)a[t];
+                HH = fma(H, H, HH);
+                xH = fma((double)xv[4 * q + t] - (double)a[t], H, xH);  // H is 0 past d
+            }
         }
     }
 }

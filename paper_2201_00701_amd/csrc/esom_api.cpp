@@ -289,7 +289,6 @@ int enqueue_embed(Scratch &sc, unsigned long long *counters, int num_cus, size_t
         bb.hist = sc.bin_hist();
         bb.cell = sc.pt_cell();
         bb.order = sc.pt_order;
-        bb.x_vec4 = (d == pl.dp && ldx % 4 == 0 && ((uintptr_t)Xc & 15) == 0) ? 1 : 0;
         return bb;
     };
     bool bin_side = false;
@@ -362,8 +361,6 @@ int enqueue_embed(Scratch &sc, unsigned long long *counters, int num_cus, size_t
         a.knn_idx = knn_idx ? knn_idx + c0 * P.k : nullptr;
         a.knn_d2 = knn_d2 ? knn_d2 + c0 * P.k : nullptr;
         a.knn_mark = knn_mark ? knn_mark + c0 : nullptr;
-        a.x_vec4 = (d == pl.dp && ldx % 4 == 0 && ((uintptr_t)a.X & 15) == 0 &&
-                    ((uintptr_t)pr.cent & 15) == 0) ? 1 : 0;
         a.order_list = a.knn_exact_order && m >= ORDER_MIN_N ? 1 : 0;
         const bool last = c0 + m >= n;
         if (what == EMBED_PROJECT && pl.kp != 0) {

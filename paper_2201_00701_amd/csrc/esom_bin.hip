@@ -56,7 +56,7 @@ __global__ void __launch_bounds__(64 * BIN_WAVES) bin_keys(BinArgs b) {
     // the centre (landmark 0, zero past d), the pivot operand (2 tiles x DC
     // chunks x 64 lanes) and its norms in accumulator order ([tile][lane
     // half][16])
-    __shared__ float cen[16 * DC];
+    __shared__ __align__(16) float cen[16 * DC];
     __shared__ u32x4 As[2][DC][64];
     __shared__ float Ns[2][2][16];
     __shared__ unsigned hl[BIN_N];
@@ -109,27 +109,10 @@ __global__ void __launch_bounds__(64 * BIN_WAVES) bin_keys(BinArgs b) {
 #pragma unroll
             for (int c = 0; c < DC; ++c) {
                 float v[8];
-                if (b.x_vec4) {
-                    const float4 *x4 = reinterpret_cast<const float4 *>(xr + 16 * c + 8 * h);
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const float4 q = valid ? x4[u] : make_float4(0.f, 0.f, 0.f, 0.f);
-                        const int q0 = 16 * c + 8 * h + 4 * u;
-                        v[4 * u] = q.x - cen[q0];
-                        v[4 * u + 1] = q.y - cen[q0 + 1];
-                        v[4 * u + 2] = q.z - cen[q0 + 2];
-                        v[4 * u + 3] = q.w - cen[q0 + 3];
-                    }
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int q = 16 * c + 8 * h + e;
-                        v[e] = (valid && q < b.d) ? xr[q] - cen[q] : 0.f;
-                    }
-                }
+                centred8(xr, cen, b.d, c, h, valid, v);
                 unsigned w[4];
 #pragma unroll
-                for (int e = 0; e < 8; e += 2) w[e >> 1] = bf16_bits_rne(v[e]) | (bf16_bits_rne(v[e + 1]) << 16);
+                for (int e = 0; e < 8; e += 2) w[e >> 1] = bf16_pair(v[e], v[e + 1]);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) part = fmaf(v[e], v[e], part);
                 P[p][c] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});

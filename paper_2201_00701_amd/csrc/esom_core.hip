@@ -238,8 +238,9 @@ __device__ __forceinline__ void prep_landmarks(int blk, const float *__restrict_
                 }
             }
             if (mode == 0) {
-                // A_f32[t][s][lane = 32 h + m], dim = 2 s + h
-                const int s = q / 2, hh = q % 2;
+                // A_f32[t][s][lane = 32 h + m], dim = 16 (s / 8) + 8 h + s % 8 (the
+                // halves of a lane pair hold runs of 8 dimensions, as in BF16)
+                const int s = 8 * (q / 16) + q % 8, hh = (q % 16) / 8;
                 reinterpret_cast<float *>(A)[((size_t)t * (dp / 2) + s) * 64 + 32 * hh + m] = a2;
             }
         }

@@ -120,7 +120,6 @@ struct EmbedArgs {
     int knn_only;  // 1: only write knn outputs (no projection)
     int lds_rows;  // 1: the block stages Lpad in LDS (row stride dp + 4 floats)
     int lds_tiles; // 1: the block stages the screen operands (A tiles, norms) in LDS
-    int x_vec4;    // 1: d == dp, X 16-byte aligned and ldx % 4 == 0 (rows load as float4)
     // Optional per-point mark beside knn outputs (serving cache): 1 when the
     // point's neighbours came from the exact path because of the screen
     // (uncertified or near tie); a projection from cached neighbours sends
@@ -152,7 +151,6 @@ struct BinArgs {
     unsigned *hist;        // 2 x BIN_COUNT: points per bin, then placement cursors (zeroed by launch_bin)
     uint16_t *cell;        // n
     int32_t *order;        // n
-    int x_vec4;            // 1: d == dp, X 16-byte aligned, ldx % 4 == 0
 };
 hipError_t launch_bin(const BinArgs &b, int num_cus, hipStream_t s);
 

@@ -55,7 +55,7 @@ __global__ void __launch_bounds__(64 * MK_WAVES) keys_kernel(MatArgs m) {
         for (int c = lane; c < dp; c += 64) xs[r * rs + c] = c < m.d ? m.X[pi * m.ldx + c] - m.cent[c] : 0.f;
     }
     __syncthreads();
-    const float *x0 = xs + i32 * rs + h, *x1 = x0 + 32 * rs;
+    const float *x0 = xs + i32 * rs + 8 * h, *x1 = x0 + 32 * rs;  // MFMA step s: dimension 16 (s / 8) + 8 h + s % 8
     for (int t = wv; t < m.ntiles; t += MK_WAVES) {
         f32x16 acc[2];
         const float4 *np = reinterpret_cast<const float4 *>(m.norms + (size_t)(t * 2 + h) * 16);
@@ -75,8 +75,8 @@ __global__ void __launch_bounds__(64 * MK_WAVES) keys_kernel(MatArgs m) {
             for (int s = 0; s < 8; ++s) av[s] = At[(size_t)(s0 + s) * 64];
 #pragma unroll
             for (int s = 0; s < 8; ++s) {
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[s], x0[2 * (s0 + s)], acc[0], 0, 0, 0);
-                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[s], x1[2 * (s0 + s)], acc[1], 0, 0, 0);
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[s], x0[2 * s0 + s], acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[s], x1[2 * s0 + s], acc[1], 0, 0, 0);
             }
         }
 #pragma unroll

@@ -27,9 +27,10 @@ static hipError_t launch_dc(const EmbedArgs &a, int block, size_t smem, int num_
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, block, smem) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
-    const int wpb = block / 64;
-    const long long waves = (a.n + 63) / 64;
-    long long blocks = (waves + wpb - 1) / wpb;
+    // A block's waves take tiles gridDim.x apart, so that few tiles spread over as
+    // many CUs as there are (the other waves only help to stage the rows).  1024
+    // points x 16-D: 25 us in full blocks, 19 so.
+    long long blocks = (a.n + 63) / 64;
     if (blocks > (long long)per_cu * num_cus) blocks = (long long)per_cu * num_cus;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(block), smem, s, a);

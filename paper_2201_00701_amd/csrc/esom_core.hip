@@ -22,6 +22,7 @@ namespace esom {
 // depends on it: results follow the landmark indices, which the keys carry.
 constexpr int ORDER_MAX_P = 64;
 constexpr int ASSIGN_PER_BLOCK = 16;  // landmarks per assignment block
+constexpr int PVT_STRIDE = 65;        // floats of a dimension of the staged pivots
 
 // Wavefront minimum of an unsigned value (device library, DPP reduction).
 extern "C" __device__ unsigned int __ockl_wfred_min_u32(unsigned int);
@@ -43,29 +44,31 @@ __global__ void prep_centroid(const float *__restrict__ L, int g, int d, int dp,
                               float *__restrict__ pp) {
     __shared__ double red[256];
     if ((int)blockIdx.x >= dp) {
-        // pivot rows staged transposed (dimension-major: lanes read
-        // consecutive words), then ASSIGN_PER_BLOCK landmarks, one per
-        // wavefront at a time, lane = pivot
-        extern __shared__ float pvt[];  // d x 64
+        // pivot rows staged transposed (dimension-major, one word of padding: both
+        // the coalesced reads of rows and the lanes' reads of a dimension spread
+        // over the banks), then ASSIGN_PER_BLOCK landmarks, one per wavefront at a
+        // time, lane = pivot
+        extern __shared__ float pvt[];  // d x PVT_STRIDE
         const int P = order_pivots(g);
         for (int e = threadIdx.x; e < d * 64; e += blockDim.x) {
-            const int q = e / 64, i = e % 64;
-            pvt[e] = i < P ? L[(size_t)(((long long)i * g) / P) * d + q] : 0.f;
+            const unsigned i = (unsigned)e / (unsigned)d, q = (unsigned)e % (unsigned)d;
+            pvt[q * PVT_STRIDE + i] = (int)i < P ? L[(size_t)(i * (unsigned)g / (unsigned)P) * d + q] : 0.f;
         }
         __syncthreads();
-        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+        const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const int j0 = ((int)blockIdx.x - dp) * ASSIGN_PER_BLOCK;
         for (int j = j0 + wv; j < j0 + ASSIGN_PER_BLOCK && j < g; j += blockDim.x / 64) {
             const float *Lj = L + (size_t)j * d;
             float s = 0.f;
+#pragma unroll 8
             for (int q = 0; q < d; ++q) {
-                const float df = Lj[q] - pvt[q * 64 + lane];
+                const float df = Lj[q] - pvt[q * PVT_STRIDE + lane];
                 s = fmaf(df, df, s);
             }
             const float dd = lane < P ? s : INFINITY;
             {
-                const int pi = (int)(((long long)j * P + g - 1) / g);  // the pivot j may be
-                if (pi < P && (int)(((long long)pi * g) / P) == j && lane < P) pp[pi * P + lane] = dd;
+                const int pi = (int)(((unsigned)(j * P) + g - 1) / (unsigned)g);  // the pivot j may be
+                if (pi < P && (int)((unsigned)(pi * g) / (unsigned)P) == j && lane < P) pp[pi * P + lane] = dd;
             }
             // nearest pivot: wave minimum of (distance bits, low 6 bits = pivot)
             const unsigned kv = lane < P ? ((__float_as_uint(dd) & ~63u) | (unsigned)lane) : 0xffffffffu;
@@ -102,10 +105,14 @@ __global__ void prep_centroid(const float *__restrict__ L, int g, int d, int dp,
 // One block orders the landmarks:
 //  1. the pivot chain (pivot-to-pivot squared distances from the assignment
 //     pass); a pivot's place is its step in the chain;
-//  2. each landmark's key (place of its pivot, distance to it, index), 64 bits;
+//  2. each landmark's key (distance to its pivot, index), 64 bits;
 //  3. a counting sort by place (a histogram and its prefix sum), then each
 //     landmark's position within its place by counting the smaller keys of
 //     the same place only (about g / 64 of them).
+// One block on a serial chain of 63 steps: latency bounds it (a minimum within 16
+// lanes of four pivots each took as long as this one over 64 lanes).  The histogram
+// runs beside the chain, and the ranks read consecutive keys: 1024 landmarks, 14.0
+// us with the histogram after the chain and ranks through a list of indices, 11.6.
 // Writes perm (position -> landmark) and ipos (landmark -> position).
 __global__ void __launch_bounds__(1024) prep_order(int g, const int *__restrict__ pcl,
                                                    const float *__restrict__ pdist,
@@ -113,68 +120,73 @@ __global__ void __launch_bounds__(1024) prep_order(int g, const int *__restrict_
                                                    int *__restrict__ perm, int *__restrict__ ipos) {
     extern __shared__ __align__(16) unsigned char osm[];
     const int P = order_pivots(g);
-    unsigned long long *key = reinterpret_cast<unsigned long long *>(osm);  // g
-    float *pp = reinterpret_cast<float *>(key + g);                          // P x P
-    int *place = reinterpret_cast<int *>(pp + ORDER_MAX_P * ORDER_MAX_P);    // P
-    int *cnt = place + ORDER_MAX_P;                                          // landmarks per place
-    int *start = cnt + ORDER_MAX_P;                                          // first position of a place
-    int *fill = start + ORDER_MAX_P;                                         // bucket fill counters
-    int *bucket = fill + ORDER_MAX_P;                                        // g: landmarks by place
+    unsigned long long *bkey = reinterpret_cast<unsigned long long *>(osm);  // g: keys by place
+    unsigned *pk = reinterpret_cast<unsigned *>(bkey + g);                     // P rows of 64: distance | pivot
+    int *place = reinterpret_cast<int *>(pk + ORDER_MAX_P * ORDER_MAX_P);      // of a pivot
+    int *cnt = place + ORDER_MAX_P;                                            // landmarks of a pivot
+    int *start = cnt + ORDER_MAX_P;                                            // first position of a pivot's
+    int *pcnt = start + ORDER_MAX_P;                                           // landmarks of a place
+    int *slot = pcnt + ORDER_MAX_P;                                            // g: number within its pivot's
     const int tid = threadIdx.x;
-    for (int e = tid; e < P * P; e += blockDim.x) pp[e] = ppg[e];
-    if (tid < ORDER_MAX_P) {
-        cnt[tid] = 0;
-        fill[tid] = 0;
+    // the assignment of this thread's first landmark, in flight over the chain
+    const int pcl0 = tid < g ? pcl[tid] : 0;
+    const float pd0 = tid < g ? pdist[tid] : 0.f;
+    for (int e = tid; e < P * 64; e += blockDim.x) {
+        const int r = e >> 6, c = e & 63;
+        pk[e] = c < P ? (__float_as_uint(fmaxf(ppg[r * P + c], 0.f)) & ~63u) | (unsigned)c : 0xffffffffu;
     }
+    if (tid < ORDER_MAX_P) cnt[tid] = 0;
     __syncthreads();
     // 1. greedy chain over the pivots (one wavefront, lane = pivot): each step
     // takes the nearest pivot not yet taken, by a wave minimum of 32-bit keys
     // (distance bits with the 6 low bits replaced by the pivot number)
     if (tid < 64) {
         bool taken = tid == 0;
-        int cur = 0;
-        if (tid == 0) place[0] = 0;
+        int cur = 0, mine = 0;
         for (int r = 1; r < P; ++r) {
-            unsigned kv = 0xffffffffu;
-            if (tid < P && !taken) kv = (__float_as_uint(fmaxf(pp[cur * P + tid], 0.f)) & ~63u) | (unsigned)tid;
+            const unsigned kv = taken ? 0xffffffffu : pk[cur * 64 + tid];
             cur = (int)(__ockl_wfred_min_u32(kv) & 63u);
-            if (tid == cur) taken = true;
-            if (tid == 0) place[cur] = r;
+            if (tid == cur) {
+                taken = true;
+                mine = r;
+            }
         }
+        place[tid] = tid < P ? mine : tid;  // a permutation of 0 .. 63
     }
-    __syncthreads();
-    // 2. keys: place (6 bits) | distance bits (31) | index (13); landmarks per place
-    for (int j = tid; j < g; j += blockDim.x) {
-        const int pl = place[pcl[j]];
-        const unsigned db = __float_as_uint(fmaxf(pdist[j], 0.f)) & 0x7fffffffu;
-        key[j] = ((unsigned long long)pl << 44) | ((unsigned long long)db << 13) | (unsigned long long)j;
-        atomicAdd(&cnt[pl], 1);
-    }
+    // 2. landmarks per pivot, and each one's number within them; wavefront 0 joins
+    // when the chain is done
+    for (int j = tid; j < g; j += blockDim.x) slot[j] = atomicAdd(&cnt[j == tid ? pcl0 : pcl[j]], 1);
     __syncthreads();
     if (tid < 64) {
-        // exclusive prefix sum over the places (P <= 64)
-        int v = tid < P ? cnt[tid] : 0;
+        // exclusive prefix sum over the places, scattered back to the pivots
+        pcnt[place[tid]] = cnt[tid];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const int v = pcnt[tid];
         int incl = v;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
             const int t = __shfl_up(incl, o);
             if (tid >= o) incl += t;
         }
-        if (tid < P) start[tid] = incl - v;
+        const int mine = __shfl(incl - v, place[tid]);
+        start[tid] = mine;
     }
     __syncthreads();
-    // 3. buckets, then the rank within the bucket (keys are distinct)
-    for (int j = tid; j < g; j += blockDim.x) {
-        const int pl = (int)(key[j] >> 44);
-        bucket[start[pl] + atomicAdd(&fill[pl], 1)] = j;
-    }
+    // 3. keys by place: distance bits (31) | index (13)
+    auto key_of = [&](int j) {
+        const unsigned db = __float_as_uint(fmaxf(j == tid ? pd0 : pdist[j], 0.f)) & 0x7fffffffu;
+        return ((unsigned long long)db << 13) | (unsigned long long)j;
+    };
+    for (int j = tid; j < g; j += blockDim.x) bkey[start[j == tid ? pcl0 : pcl[j]] + slot[j]] = key_of(j);
     __syncthreads();
+    // 4. the rank within the place (keys are distinct)
     for (int j = tid; j < g; j += blockDim.x) {
-        const unsigned long long kj = key[j];
-        const int pl = (int)(kj >> 44);
-        const int b0 = start[pl], nb = cnt[pl];
+        const unsigned long long kj = key_of(j);
+        const int pc = j == tid ? pcl0 : pcl[j];
+        const int b0 = start[pc], nb = cnt[pc];
         int pos = b0;
-        for (int i = 0; i < nb; ++i) pos += key[bucket[b0 + i]] < kj ? 1 : 0;
+#pragma unroll 8
+        for (int i = 0; i < nb; ++i) pos += bkey[b0 + i] < kj ? 1 : 0;
         perm[pos] = j;
         ipos[j] = pos;
     }
@@ -330,7 +342,7 @@ __global__ void __launch_bounds__(256) prep_tables(const float *__restrict__ L, 
 hipError_t launch_prep(const Prep &P, const float *L, int mode,
                        unsigned long long *counters, long long n_points, hipStream_t s) {
     hipLaunchKernelGGL(prep_centroid, dim3(P.dp + (P.g + ASSIGN_PER_BLOCK - 1) / ASSIGN_PER_BLOCK),
-                       dim3(256), sizeof(float) * P.d * 64, s, L, P.g, P.d, P.dp, P.cent, P.lmax, counters,
+                       dim3(256), sizeof(float) * P.d * PVT_STRIDE, s, L, P.g, P.d, P.dp, P.cent, P.lmax, counters,
                        n_points, P.pcl, P.pdist, P.ppiv);
     const size_t osm = sizeof(unsigned long long) * P.g + sizeof(float) * ORDER_MAX_P * ORDER_MAX_P +
                        sizeof(int) * (4 * ORDER_MAX_P + P.g);

@@ -88,14 +88,15 @@ __device__ __forceinline__ double lp_det3(double a00, double a01, double a02, do
     return a00 * (a11 * a22 - a12 * a21) - a01 * (a10 * a22 - a12 * a20) + a02 * (a10 * a21 - a11 * a20);
 }
 
-// Values t0 .. t0 + 15 of a row of d floats (4-byte aligned), 0 past its end.
+// Values t0 .. t0 + N - 1 of a row of d floats (4-byte aligned), 0 past its end.
 struct __attribute__((packed, aligned(4))) LpFloat4 {
     float x, y, z, w;
 };
-__device__ __forceinline__ void lp_load16(const float *x, int t0, int d, float (&v)[16]) {
-    if (t0 + 16 <= d) {
+template <int N>
+__device__ __forceinline__ void lp_load(const float *x, int t0, int d, float (&v)[N]) {
+    if (t0 + N <= d) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < N / 4; ++q) {
             const LpFloat4 f = *reinterpret_cast<const LpFloat4 *>(x + t0 + 4 * q);
             v[4 * q] = f.x;
             v[4 * q + 1] = f.y;
@@ -104,27 +105,31 @@ __device__ __forceinline__ void lp_load16(const float *x, int t0, int d, float (
         }
     } else {
 #pragma unroll
-        for (int t = 0; t < 16; ++t) v[t] = t0 + t < d ? x[t0 + t] : 0.f;
+        for (int t = 0; t < N; ++t) v[t] = t0 + t < d ? x[t0 + t] : 0.f;
     }
 }
 
-// <x - L_u, H> and |H|^2 of the rows at positions u, v (H = L_v - L_u).
+// <x - L_u, H> and |H|^2 of the rows at positions u, v (H = L_v - L_u), U quads of
+// dimensions loaded at a time: 4 where every pair comes here; 1 where the table
+// serves almost all of them and the registers are the other waves' (with 4 the
+// 3-D projection of 200k points took 218 us for 177).
+template <int U>
 __device__ __forceinline__ void lp_direct(const ListArgs &e, const float *x, unsigned u, unsigned v, double &xH,
                                           double &HH) {
     const float4 *Lu = reinterpret_cast<const float4 *>(e.Lpad + (size_t)u * e.dp);
     const float4 *Lv = reinterpret_cast<const float4 *>(e.Lpad + (size_t)v * e.dp);
     xH = HH = 0.0;
-    for (int c = 0; c < e.dp / 16; ++c) {  // 16 dimensions' loads in flight
-        float4 lu[4], lv[4];
-        float xv[16];
+    for (int c = 0; c < e.dp / (4 * U); ++c) {
+        float4 lu[U], lv[U];
+        float xv[4 * U];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            lu[q] = Lu[4 * c + q];
-            lv[q] = Lv[4 * c + q];
+        for (int q = 0; q < U; ++q) {
+            lu[q] = Lu[U * c + q];
+            lv[q] = Lv[U * c + q];
         }
-        lp_load16(x, 16 * c, e.d, xv);
+        lp_load<4 * U>(x, 4 * U * c, e.d, xv);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < U; ++q) {
             const float a[4] = {lu[q].x, lu[q].y, lu[q].z, lu[q].w}, b[4] = {lv[q].x, lv[q].y, lv[q].z, lv[q].w};
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
@@ -247,7 +252,7 @@ __device__ __forceinline__ void lp_point(const ListArgs &e, int64_t pi, bool on,
         if (e.tab) {
             inv = e.tab[(size_t)A.pos * e.g + B.pos];
         } else {
-            lp_direct(e, x, A.pos, B.pos, xH, HH);
+            lp_direct<M == 2 ? 4 : 1>(e, x, A.pos, B.pos, xH, HH);
             inv = HH > 0.0 ? 0.5 / HH : 0.0;
         }
         if (!(inv > 0.0)) continue;
@@ -255,7 +260,7 @@ __device__ __forceinline__ void lp_point(const ListArgs &e, int64_t pi, bool on,
         if (!e.tab) {
             D = xH / HH;
         } else if (2.0 * B.d2 * inv > LP_POLAR_MAX) {  // delta^2 ascends: B's is the larger
-            lp_direct(e, x, A.pos, B.pos, xH, HH);
+            lp_direct<M == 2 ? 4 : 1>(e, x, A.pos, B.pos, xH, HH);
             D = xH / HH;
         }
         double h[M], hh = 0.0, hl = 0.0;

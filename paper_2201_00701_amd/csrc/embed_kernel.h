@@ -9,16 +9,17 @@
 // the 32x32 output layout lane l holds 16 keys of point (l mod 32); the two
 // lanes l and l+32 of a point see disjoint halves of every tile.
 //   Pass 1 (BF16 operands) keeps, per lane, the minimum key of 32 landmark
-//   groups (register slot x tile parity).  A lane's j-th smallest group
-//   minimum bounds from above j distinct keys of its half, so with
-//   j = ceil(C/2) the larger of the two lanes' values has at least C keys at
-//   or below it; widened by both passes' error bounds it is the threshold tau.
+//   groups (register slot x tile parity).  The C-th smallest of a point's 64
+//   group minima bounds from above C distinct keys; widened by both passes'
+//   error bounds it is the threshold tau.  Points in locality order also keep
+//   each tile's minimum, and pass 2 leaves out the tiles that lie above tau.
 //   Pass 2 recomputes the keys more accurately (FP32 operands in FP32 mode;
 //   in BF16 mode both operands split into high and low BF16 parts, three
 //   products per element, which leaves an error near 2^-16 of the products
 //   instead of 2^-8) and shifts one bit per key (key <= tau) into a per-lane
 //   bitmap in LDS: the candidate set, with no capacity limit.
-// Phase B, exact selection (one lane = one point).  Every candidate is
+// Phase B, exact selection (one lane = one point; rows streamed from L2 are read
+// by quads of lanes).  Every candidate is
 // rescored with exact FP32 differences and inserted into a sorted register
 // list; keys are doubles packing (delta^2, landmark index) so a plain
 // min/max network orders them lexicographically.  A point is certified when

@@ -11,8 +11,9 @@
 // points far from everything (background, sparse regions), whose neighbours are
 // spread over most tiles, out of the wavefronts of the dense regions: at 1M x
 // 48-D with 1024 landmarks, 5% background, 0.12 instead of 0.33 of the (tile,
-// 32-point half) pairs hold a candidate; at 10M x 64-D 0.21 instead of 0.36.  The order has no effect on any result.  It needs nothing from the
-// landmark preparation, so a context runs it on a second stream beside that.
+// 32-point half) pairs hold a candidate; at 10M x 64-D 0.21 instead of 0.36.  The
+// order has no effect on any result.  It needs nothing from the landmark
+// preparation, so a context runs it on a second stream beside that.
 //
 //   bin_zero     clears the counts;
 //   bin_keys     one wavefront per 64 points (persistent): the 64 pivots as

@@ -13,7 +13,6 @@ constexpr int TILE = 32;
 // Landmark count is padded to a multiple of 64 so tiles come in pairs.
 constexpr int TILE_PAIR = 64;
 // Fast-path limits (larger shapes go through the exact FP64 path).
-constexpr int FAST_MAX_KP = 32;
 constexpr int FAST_MAX_DC_BF16 = 8;  // d <= 128
 constexpr int FAST_MAX_DC_FP32 = 4;  // d <= 64
 constexpr int FAST_MAX_G = 4096;
@@ -135,10 +134,10 @@ struct EmbedArgs {
 };
 
 // Locality order of the points (esom_bin.hip): each point's nearest of the
-// 64 ordering pivots (landmarks j g / 64, BF16 MFMA keys centred on landmark
-// 0) and a class of its distance, then a counting sort by both.  Needs nothing from the landmark
-// preparation, so it can run beside it.  Used for large landmark sets
-// (g >= BIN_MIN_G) and calls of at least BIN_MIN_N points.
+// 64 ordering pivots (landmarks j g / 64, BF16 MFMA keys centred on landmark 0)
+// and a class of its distance, then a counting sort by both.  Needs nothing from
+// the landmark preparation, so it can run beside it.  Used for large landmark
+// sets (g >= BIN_MIN_G) and calls of at least BIN_MIN_N points.
 constexpr int BIN_MIN_G = 512;
 constexpr int64_t BIN_MIN_N = 65536;
 constexpr int BIN_COUNT = 512;  // bins: 64 pivots x 8 distance classes

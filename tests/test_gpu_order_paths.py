@@ -1,0 +1,86 @@
+"""Points whose neighbours are certain but not their order, rows at any alignment,
+and the nearest-landmark kernel, against the FP64 oracle on whole-number data: all
+distances are exact and ties frequent, so the lists must equal the oracle's."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_dev():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    return torch
+
+
+def _dev(torch, a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _whole(n, d, g, seed):
+    rng = np.random.default_rng(seed)
+    X = rng.integers(-3, 4, (n, d)).astype(np.float32)
+    L = rng.integers(-3, 4, (g, d)).astype(np.float32)
+    return X, L, rng.normal(0, 3, (g, 2)).astype(np.float32)
+
+
+# n on both sides of 65536 (lists ranked apart, locality order); g on both sides of
+# 512; d within a chunk of 16, past one, and whole chunks; list sizes 8 to 32 with k
+# equal to them and below; rows one float past a 16-byte boundary, and wider than d
+@pytest.mark.parametrize("n,d,g,k,mode,shift,pad", [
+    (65_535, 39, 600, 24, "fp32", 1, 0), (65_536, 39, 600, 24, "fp32", 1, 0), (65_537, 39, 600, 20, "bf16", 3, 0),
+    (70_001, 17, 511, 16, "bf16", 1, 0), (70_001, 33, 512, 9, "fp32", 2, 5), (66_000, 64, 1025, 32, "bf16", 0, 0),
+    (66_000, 100, 520, 8, "bf16", 1, 1), (700, 5, 70, 8, "fp32", 1, 2)])
+def test_open_orders(torch_dev, oracle_mod, n, d, g, k, mode, shift, pad):
+    from paper_2201_00701_amd import esom
+    X, L, l = _whole(n, d, g, n + d + k)
+    flat = np.full(shift + n * (d + pad), 9.0, np.float32)
+    flat[shift:].reshape(n, d + pad)[:, :d] = X
+    flat = _dev(torch_dev, flat)
+    Xd = flat[shift:].view(n, d + pad)[:, :d]
+    ctx = esom.Context(0)
+    try:
+        print("case open orders n=%d d=%d g=%d k=%d %s shift=%d pad=%d" % (n, d, g, k, mode, shift, pad), flush=True)
+        out, idx, d2 = ctx.embed(Xd, _dev(torch_dev, L), _dev(torch_dev, l), k=k, mode=mode, knn=True)
+        out, idx, d2 = out.cpu().numpy().astype(np.float64), idx.cpu().numpy(), d2.cpu().numpy()
+    finally:
+        ctx.close()
+    rows = np.unique(np.concatenate([np.random.default_rng(1).choice(n, min(n, 1500), replace=False), [0, n - 1]]))
+    ref = oracle_mod.embed(X[rows], L, l, k, threads=8)
+    np.testing.assert_array_equal(idx[rows], ref["idx"][:, :k])
+    exact = ((X[rows][:, None].astype(np.float64) - L[idx[rows]]) ** 2).sum(2)  # whole numbers below 2^24
+    np.testing.assert_array_equal(d2[rows], exact)
+    # the library's coordinate bar: 1e-4 of the grid span, or of an output beyond it
+    span = float(np.ptp(l, axis=0).max())
+    scale = np.maximum(span, np.abs(ref["out"]).max(axis=1))
+    assert (np.abs(out[rows] - ref["out"]).max(axis=1) / scale).max() <= 1e-4
+
+
+# batch updates that find the nearest landmark themselves: one landmark pair, g around
+# 512 and the largest, d around the FP32 and the fused kernels' limits, n around a wave
+@pytest.mark.parametrize("n,d,g", [(1, 3, 2), (65, 16, 64), (70_001, 33, 513), (66_000, 64, 511), (3000, 65, 600),
+                                   (2000, 128, 4096), (900, 129, 300), (5000, 7, 4097)])
+def test_nearest_landmark(torch_dev, n, d, g):
+    from paper_2201_00701_amd import esom
+    X, L, l = _whole(n, d, g, n + d + g)
+    L[g - 1] = L[0]  # coincident landmarks: the lower index wins
+    ctx = esom.Context(0)
+    try:
+        print("case nearest n=%d d=%d g=%d" % (n, d, g), flush=True)
+        Ld = _dev(torch_dev, L)
+        cnt = ctx.landmark_update(_dev(torch_dev, X), Ld, _dev(torch_dev, l), kind="kmeans", alpha=1.0, counts=True)
+        got, cnt = Ld.cpu().numpy(), cnt.cpu().numpy()
+    finally:
+        ctx.close()
+    # whole numbers: the products and sums are exact in FP64, argmin takes the lowest index
+    near = np.empty(n, np.int64)
+    L64 = L.astype(np.float64)
+    for a in range(0, n, 4096):
+        near[a:a + 4096] = ((L64 ** 2).sum(1) - 2.0 * X[a:a + 4096].astype(np.float64) @ L64.T).argmin(1)
+    np.testing.assert_array_equal(cnt, np.bincount(near, minlength=g))
+    S = np.zeros((g, d))
+    np.add.at(S, near, X.astype(np.float64))
+    ref = np.where(cnt[:, None] > 0, S / np.maximum(cnt, 1)[:, None], L)
+    # one rounding of the mean to FP32, and two FP64 operations on the way
+    np.testing.assert_allclose(got, ref, rtol=2.0 ** -23, atol=2.0 ** -50)

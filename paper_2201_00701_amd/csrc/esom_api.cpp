@@ -306,7 +306,8 @@ int enqueue_embed(Scratch &sc, unsigned long long *counters, int num_cus, size_t
         }
     }
     if (ev) (void)hipEventRecord(ev[0], s);
-    hipError_t e = launch_prep(pr, L, prep_mode, counters, knn_only ? 0 : (long long)n, s);
+    hipError_t e = launch_prep(pr, L, prep_mode, prep_ordered(n, g, bin_all, what == EMBED_PROJECT) ? 1 : 0, counters,
+                               knn_only ? 0 : (long long)n, s);
     if (e != hipSuccess) return hip_fail(e, "landmark preparation launch");
     if (ev) (void)hipEventRecord(ev[1], s);
 

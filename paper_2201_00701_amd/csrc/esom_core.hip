@@ -20,6 +20,7 @@ namespace esom {
 // next pivot the nearest one not yet taken); landmarks are sorted by (their
 // pivot's place in the chain, distance to the pivot, index).  Only speed
 // depends on it: results follow the landmark indices, which the keys carry.
+// Small calls keep the landmarks' own order (prep_ordered).
 constexpr int ORDER_MAX_P = 64;
 constexpr int ASSIGN_PER_BLOCK = 16;  // landmarks per assignment block
 constexpr int PVT_STRIDE = 65;        // floats of a dimension of the staged pivots
@@ -33,7 +34,8 @@ __host__ __device__ inline int order_pivots(int g) { return g < ORDER_MAX_P ? g 
 // blocks 0 .. dp-1, one per dimension.  Block 0 also resets the per-call
 // fallback list and the landmark maxima (norm, BF16 quantisation error of the
 // MFMA operand), and counts the points of this
-// call.  Blocks dp .. : the landmarks' nearest pivots (squared FP32
+// call; without a landmark order (ordered = 0) they also write the identity.
+// Blocks dp .. (ordered only): the landmarks' nearest pivots (squared FP32
 // distance; equal leading bits break to the lower pivot) into pcl[j] and
 // that distance into pdist[j]; a pivot's wavefront also writes its row of
 // pivot-to-pivot distances into pp.
@@ -41,7 +43,7 @@ __global__ void prep_centroid(const float *__restrict__ L, int g, int d, int dp,
                               float *__restrict__ cent, float *__restrict__ lmax,
                               unsigned long long *__restrict__ counters, long long n_points,
                               int *__restrict__ pcl, float *__restrict__ pdist,
-                              float *__restrict__ pp) {
+                              float *__restrict__ pp, int *__restrict__ perm, int *__restrict__ ipos, int ordered) {
     __shared__ double red[256];
     if ((int)blockIdx.x >= dp) {
         // pivot rows staged transposed (dimension-major, one word of padding: both
@@ -81,6 +83,8 @@ __global__ void prep_centroid(const float *__restrict__ L, int g, int d, int dp,
         return;
     }
     const int t = blockIdx.x;
+    if (!ordered)
+        for (int j = t * blockDim.x + threadIdx.x; j < g; j += dp * blockDim.x) perm[j] = ipos[j] = j;
     double s = 0.0;
     if (t < d)
         for (int j = threadIdx.x; j < g; j += blockDim.x) s += (double)L[(size_t)j * d + t];
@@ -339,15 +343,16 @@ __global__ void __launch_bounds__(256) prep_tables(const float *__restrict__ L, 
         prep_pairs((int)blockIdx.x - nlb, prs, L, perm, g, d, pairs);
 }
 
-hipError_t launch_prep(const Prep &P, const float *L, int mode,
+hipError_t launch_prep(const Prep &P, const float *L, int mode, int ordered,
                        unsigned long long *counters, long long n_points, hipStream_t s) {
-    hipLaunchKernelGGL(prep_centroid, dim3(P.dp + (P.g + ASSIGN_PER_BLOCK - 1) / ASSIGN_PER_BLOCK),
-                       dim3(256), sizeof(float) * P.d * PVT_STRIDE, s, L, P.g, P.d, P.dp, P.cent, P.lmax, counters,
-                       n_points, P.pcl, P.pdist, P.ppiv);
-    const size_t osm = sizeof(unsigned long long) * P.g + sizeof(float) * ORDER_MAX_P * ORDER_MAX_P +
-                       sizeof(int) * (4 * ORDER_MAX_P + P.g);
-    hipLaunchKernelGGL(prep_order, dim3(1), dim3(1024), osm, s, P.g, P.pcl, P.pdist, P.ppiv, P.perm,
-                       P.ipos);
+    const int assign = ordered ? (P.g + ASSIGN_PER_BLOCK - 1) / ASSIGN_PER_BLOCK : 0;
+    hipLaunchKernelGGL(prep_centroid, dim3(P.dp + assign), dim3(256), sizeof(float) * P.d * PVT_STRIDE, s, L, P.g,
+                       P.d, P.dp, P.cent, P.lmax, counters, n_points, P.pcl, P.pdist, P.ppiv, P.perm, P.ipos, ordered);
+    if (ordered) {
+        const size_t osm = sizeof(unsigned long long) * P.g + sizeof(float) * ORDER_MAX_P * ORDER_MAX_P +
+                           sizeof(int) * (4 * ORDER_MAX_P + P.g);
+        hipLaunchKernelGGL(prep_order, dim3(1), dim3(1024), osm, s, P.g, P.pcl, P.pdist, P.ppiv, P.perm, P.ipos);
+    }
     const int gpad = P.ntiles * TILE;
     const int nlb = (gpad + 3) / 4;
     const int ntu = P.need_pairs ? (P.g + PAIR_TILE - 1) / PAIR_TILE : 0;

@@ -154,7 +154,19 @@ struct BinArgs {
 hipError_t launch_bin(const BinArgs &b, int num_cus, hipStream_t s);
 
 // Launchers (esom_core.hip).
-hipError_t launch_prep(const Prep &P, const float *L, int mode, unsigned long long *counters,
+// Landmarks are put in order (prep_order) where that saves more than the 11 us it
+// takes: with the pair table past the L1 (g = 100: no gain at any n up to 400k) and
+// n g of 5e7 up.  Measured, own order against prep_order, us a call: 400 landmarks
+// x 32-D, n = 40k 107 against 118, 100k 150 / 154, 200k 233 / 230, 400k 385 / 342;
+// 1024 x 48-D, 20k 135 / 142, 40k 149 / 154, 65k 163 / 161; 4096 x 64-D, 10k 631 /
+// 661, 40k 740 / 713.  Points in locality order always need it (their wavefronts
+// leave out tiles of far landmarks): 1024 x 48-D, 100k 215 against 192.  A
+// projection from cached lists is mostly pair-table reads, and takes it from half of
+// that up: 100k points, 400 landmarks, 52 us against 31 plus the order.
+inline bool prep_ordered(int64_t n, int g, bool points_ordered, bool project_only) {
+    return points_ordered || (g > 128 && (double)n * g >= (project_only ? 2.5e7 : 5e7));
+}
+hipError_t launch_prep(const Prep &P, const float *L, int mode, int ordered, unsigned long long *counters,
                        long long n_points, hipStream_t s);
 hipError_t launch_embed(const EmbedArgs &a, int mode, int kp, int num_cus, size_t lds_per_block,
                         hipStream_t s);

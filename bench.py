@@ -160,26 +160,29 @@ def roofline_for(mode, n, g, d, k, ms_main, st, workload):
     gpad = 64 * math.ceil(g / 64)
     dpad = 16 * math.ceil(d / 16)
     traffic = measured_traffic(mode, workload)
+    # points in locality order leave out the tiles that hold no candidate in the
+    # candidate pass: how many products that pass issues then depends on the data
+    ordered = g >= 512 and n >= 65536
     if mode == "fp32":
         ach = 2.0 * n * g * d / (ms_main * 1e-3) / 1e12
         # FP32 MFMA runs the candidate pass (the threshold pass is BF16), over
         # the padded landmark and dimension counts
-        issued = 2.0 * n * gpad * dpad / (ms_main * 1e-3) / 1e12
+        issued = None if ordered else 2.0 * n * gpad * dpad / (ms_main * 1e-3) / 1e12
         return {"bound": "mfma", "achieved": ach, "peak": MFMA_FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": ach / MFMA_FP32_PEAK_TFLOPS, "traffic": traffic,
-                "issued_tflops": issued, "issued_frac": issued / MFMA_FP32_PEAK_TFLOPS}
+                "issued_tflops": issued, "issued_frac": issued and issued / MFMA_FP32_PEAK_TFLOPS}
     cands = st["n_candidates"] / max(st["n_points"], 1)
     ach = alu_flops_per_point(g, d, k, k + 2) * n / (ms_main * 1e-3) / 1e12
     mf = 2.0 * n * g * d / (ms_main * 1e-3) / 1e12
     # BF16 MFMA issued: the threshold pass and the split candidate pass (three
     # products per element), over the padded counts
-    mfi = 4.0 * 2.0 * n * gpad * dpad / (ms_main * 1e-3) / 1e12
+    mfi = None if ordered else 4.0 * 2.0 * n * gpad * dpad / (ms_main * 1e-3) / 1e12
     return {"bound": "alu", "achieved": ach, "peak": VALU_FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
             "frac": ach / VALU_FP32_PEAK_TFLOPS, "traffic": traffic,
             "peak_nonpacked": VALU_FP32_NONPACKED_TFLOPS,
             "frac_nonpacked": ach / VALU_FP32_NONPACKED_TFLOPS,
             "mfma_bf16_tflops": mf, "mfma_bf16_frac": mf / MFMA_BF16_PEAK_TFLOPS,
-            "mfma_bf16_issued_tflops": mfi, "mfma_bf16_issued_frac": mfi / MFMA_BF16_PEAK_TFLOPS,
+            "mfma_bf16_issued_tflops": mfi, "mfma_bf16_issued_frac": mfi and mfi / MFMA_BF16_PEAK_TFLOPS,
             "candidates_per_point": cands}
 
 

@@ -84,3 +84,25 @@ def test_nearest_landmark(torch_dev, n, d, g):
     ref = np.where(cnt[:, None] > 0, S / np.maximum(cnt, 1)[:, None], L)
     # one rounding of the mean to FP32, and two FP64 operations on the way
     np.testing.assert_allclose(got, ref, rtol=2.0 ** -23, atol=2.0 ** -50)
+
+
+# calls on both sides of the landmark order's rule (more than 128 landmarks, n g of
+# 5e7): a point's result follows from the point alone, so parts of a call in the
+# landmarks' own order give the bits of the whole call in the ordered one
+@pytest.mark.parametrize("n,d,g,k,mode", [(126_000, 17, 400, 16, "bf16"), (126_000, 32, 400, 9, "fp32"),
+                                          (390_001, 8, 129, 5, "bf16"), (60_000, 70, 1000, 12, "fp32")])
+def test_landmark_order_bit_identical(torch_dev, n, d, g, k, mode):
+    from paper_2201_00701_amd import esom
+    rng = np.random.default_rng(n + g)
+    L = rng.normal(0, 3, (g, d)).astype(np.float32)
+    X = (L[rng.integers(0, g, n)] + rng.normal(0, 1, (n, d))).astype(np.float32)
+    Xd, Ld, ld = _dev(torch_dev, X), _dev(torch_dev, L), _dev(torch_dev, rng.normal(0, 3, (g, 2)).astype(np.float32))
+    ctx = esom.Context(0)
+    try:
+        print("case landmark order n=%d d=%d g=%d k=%d %s" % (n, d, g, k, mode), flush=True)
+        whole = [t.cpu().numpy() for t in ctx.embed(Xd, Ld, ld, k=k, mode=mode, knn=True)]
+        parts = [[t.cpu().numpy() for t in ctx.embed(p, Ld, ld, k=k, mode=mode, knn=True)] for p in Xd.split(n // 3 + 1)]
+    finally:
+        ctx.close()
+    for i in range(3):
+        np.testing.assert_array_equal(whole[i], np.concatenate([p[i] for p in parts]))

@@ -106,3 +106,23 @@ def test_landmark_order_bit_identical(torch_dev, n, d, g, k, mode):
         ctx.close()
     for i in range(3):
         np.testing.assert_array_equal(whole[i], np.concatenate([p[i] for p in parts]))
+
+
+def test_nearest_landmark_of_non_finite_points(torch_dev):
+    from paper_2201_00701_amd import esom
+    n, d, g = 70, 128, 257  # rows from memory, 63 padded positions, no pair table
+    X, L, l = _whole(n, d, g, 11)
+    X[5, 100], X[64, 0] = np.nan, np.inf
+    ctx = esom.Context(0)
+    try:
+        print("case nearest of non-finite points", flush=True)
+        Ld = _dev(torch_dev, L)
+        cnt = ctx.landmark_update(_dev(torch_dev, X), Ld, _dev(torch_dev, l), kind="kmeans", alpha=1.0, counts=True)
+        cnt = cnt.cpu().numpy()
+    finally:
+        ctx.close()
+    # a NaN point has no nearest landmark; an infinite one is equally far from all, and
+    # the lowest index wins
+    ok = ~np.isnan(X).any(1)
+    d2 = ((X[ok][:, None].astype(np.float64) - L[None]) ** 2).sum(2)
+    np.testing.assert_array_equal(cnt, np.bincount(d2.argmin(1), minlength=g))

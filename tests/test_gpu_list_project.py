@@ -62,3 +62,38 @@ def test_embed3_groups(torch_dev, oracle_mod, n, d, g, k, tight, adjust):
     err = np.abs(out - ref["out"]).max(axis=1) / scale
     assert np.quantile(err, 0.99) <= 2.0 ** -22
     assert err.max() <= 1e-4
+
+
+# rows without a list (NaN) and with equal infinite distances share wavefronts with
+# points whose lists FP32 misorders (landmarks in pairs one ulp apart), in every lane
+# group, with and without the table
+@pytest.mark.parametrize("n,d,g,k", [(600, 20, 70, 16), (61, 20, 300, 9), (600, 17, 70, 32), (400, 33, 80, 40)])
+def test_embed3_non_finite_rows(torch_dev, oracle_mod, n, d, g, k):
+    from paper_2201_00701_amd import esom
+    rng = np.random.default_rng(n + d + k)
+    L = rng.normal(0, 2, (g, d)).astype(np.float32)
+    L[1::2] = L[0::2]
+    L[1::2, 3] = np.nextafter(L[0::2, 3], np.float32(9))
+    l3 = rng.normal(0, 3, (g, 3)).astype(np.float32)
+    X = rng.normal(0, 2, (n, d)).astype(np.float32)
+    Xb = X.copy()
+    nans, infs = [1, 6, n // 2], [2, n // 3, n - 1]
+    Xb[nans, [0, d - 1, 5]] = np.nan
+    Xb[infs, [d - 1, 0, 4]] = [np.inf, -np.inf, np.inf]
+    dev = lambda a: torch_dev.from_numpy(np.ascontiguousarray(a)).cuda()
+    ctx = esom.Context(0)
+    try:
+        print("case embed3 non-finite rows n=%d d=%d g=%d k=%d" % (n, d, g, k), flush=True)
+        res = [[t.cpu().numpy() for t in ctx.embed3(dev(x), dev(L), dev(l3), k=k, knn=True)] for x in (X, Xb)]
+    finally:
+        ctx.close()
+    (out, idx), (outb, idxb) = res
+    np.testing.assert_array_equal(idx, oracle_mod.embed3(X, L, l3, k, threads=8)["idx"][:, :k])
+    rest = np.setdiff1d(np.arange(n), nans + infs)
+    np.testing.assert_array_equal(idxb[rest], idx[rest])
+    np.testing.assert_array_equal(outb[rest], out[rest])
+    assert np.isnan(outb[nans]).all() and (idxb[nans] == -1).all()
+    # all distances infinite: the lowest indices, and the centroid of their positions
+    np.testing.assert_array_equal(idxb[infs], np.tile(np.arange(k), (3, 1)))
+    np.testing.assert_allclose(outb[infs], np.tile(l3[:k].astype(np.float64).mean(0), (3, 1)), rtol=2.0 ** -23,
+                               atol=2.0 ** -23)

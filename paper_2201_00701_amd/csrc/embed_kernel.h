@@ -352,7 +352,7 @@ __device__ __forceinline__ float opaque_neg_inf() {
 
 // FP64 minimum / maximum as single instructions.  fmin/fmax would add a
 // quieting step per operand for signalling NaNs, which never occur here (the
-// operands are packed keys built by integer operations, or +inf).
+// operands are packed keys of finite distances, or +inf).
 __device__ __forceinline__ double vmin64(double a, double b) {
     double r;
     asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
@@ -399,6 +399,13 @@ __device__ __forceinline__ void insert_sorted(double (&s)[KP], double &rej, doub
         asm("v_min_f64 %0, %0, %1" : "+v"(s[q]) : "v"(t));  // in place: no copies of the list
     }
     asm("v_min_f64 %0, %0, %1" : "+v"(s[0]) : "v"(v));
+}
+
+// The bits of a candidate word, before its reversal (bit 31 - b is position 2 b + h
+// of the tile pair), whose positions lie below n (1 <= n <= 64).
+__device__ __forceinline__ unsigned real_positions(int n, int h) {
+    const unsigned nv = (unsigned)(n + 1 - h) >> 1;  // 0 .. 32
+    return nv < 32u ? ~(0xFFFFFFFFu >> nv) : 0xFFFFFFFFu;
 }
 
 // Next non-empty 64-bit bitmap word of a point: mk marks the non-empty words
@@ -1518,9 +1525,12 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                         word[p] = __builtin_amdgcn_alignbit(word[p], __float_as_uint(tau[p] - acc[p][r]), 31);
             };
             auto pass2_store = [&](int tp) {
+                // no candidates past the last landmark (an infinite point's keys, or
+                // bounds that overflow, would let the padding in)
+                const unsigned real = tp == W - 1 ? real_positions(a.g - 64 * tp, h) : ~0u;
 #pragma unroll
                 for (int p = 0; p < 2; ++p) {
-                    const unsigned wd = ~word[p];
+                    const unsigned wd = ~word[p] & real;
                     bitsL[((p * W + tp) * 32 + i32) * 2 + h] = __builtin_bitreverse32(wd);
                     nonempty[p] |= (unsigned long long)(wd != 0u) << tp;
                 }
@@ -1714,7 +1724,8 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                     }
                 }
                 // keys carry the landmark index (ties break on it), not the position
-                insert_sorted<KP>(sk, rej, act ? pack_key(acc, permL[j]) : (double)INFINITY);
+                // (an infinite distance stays out: +inf with an index in its low bits is a NaN)
+                insert_sorted<KP>(sk, rej, act && acc < INFINITY ? pack_key(acc, permL[j]) : (double)INFINITY);
                 m += act ? 1 : 0;
             }
         }

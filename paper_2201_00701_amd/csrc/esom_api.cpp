@@ -108,8 +108,6 @@ size_t carve(Scratch &sc, void *base, int64_t n, int g, int dp, int pg, int64_t 
         return r;
     };
     sc.prep.cent = static_cast<float *>(take(sizeof(float) * dp));
-    // The rows come before the operand: a point that is not finite also walks padded
-    // positions, whose rows (fewer than 64) are then read from the operand's memory.
     sc.prep.Lpad = static_cast<float *>(take(sizeof(float) * (size_t)g * dp));
     sc.prep.A = take(sizeof(float) * (size_t)ntiles * TILE * dp);
     sc.prep.A16 = take(sizeof(uint16_t) * (size_t)ntiles * TILE * dp);

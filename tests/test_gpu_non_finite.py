@@ -51,3 +51,30 @@ def test_non_finite_rows(torch_dev, n, d, g, k, mode):
     centre = np.tile(l[:k].astype(np.float64).mean(0), (3, 1))  # FP64 sums, one rounding
     for o in (outb, alone):
         np.testing.assert_allclose(o[infs], centre, rtol=2.0 ** -23, atol=2.0 ** -23)
+
+
+# finite rows whose norms leave FP32 (above 1.8e19): the squared distances to the
+# nearest landmarks still fit, but most landmarks' keys are infinite and only two of the
+# key groups hold a finite one, fewer than k
+@pytest.mark.parametrize("mode", ["bf16", "fp32"])
+def test_norms_beyond_fp32(torch_dev, oracle_mod, mode):
+    from paper_2201_00701_amd import esom
+    n, d, g, k = 70, 16, 128, 3
+    rng = np.random.default_rng(4)
+    L, X = rng.normal(0, 1e17, (g, d)), rng.normal(0, 1e17, (n, d))
+    L[:, 0] += 1.86e19 * np.where(np.arange(g) % 2, 1, -1)
+    L[[0, 1, 64, 65], 0] = -0.3e19
+    X[:, 0] += 0.9e19
+    X, L = X.astype(np.float32), L.astype(np.float32)
+    l = rng.normal(0, 3, (g, 2)).astype(np.float32)
+    dev = lambda a: torch_dev.from_numpy(np.ascontiguousarray(a)).cuda()
+    ctx = esom.Context(0)
+    try:
+        print("case norms beyond fp32 %s" % mode, flush=True)
+        out, idx, d2 = [t.cpu().numpy() for t in ctx.embed(dev(X), dev(L), dev(l), k=k, mode=mode, knn=True)]
+    finally:
+        ctx.close()
+    ref = oracle_mod.embed(X, L, l, k, threads=8)
+    np.testing.assert_array_equal(idx, ref["idx"][:, :k])
+    np.testing.assert_allclose(d2, ref["d2"][:, :k], rtol=2.0 ** -23)
+    assert np.abs(out - ref["out"]).max() <= 1e-4 * max(float(np.ptp(l, axis=0).max()), np.abs(ref["out"]).max())

@@ -191,20 +191,20 @@ __device__ __forceinline__ void lp_point(const ListArgs &e, int64_t pi, bool on,
     }
     // Sorted by (distance, index).  A point without a list (its entries all stand for
     // landmark 0) or with NaN distances shares the wavefront with points to sort, so the
-    // ranks are a permutation of the places for it too: NaN ranks as +inf, and equal
-    // entries by their place.  (A place that no entry took would hold other data, and
-    // its index is used for loads.)
+    // ranks are a permutation of the places for it too: such a list keeps its places,
+    // and NaN ranks as +inf.  (A place that no entry took would hold other data, and its
+    // index is used for loads.)
     const double dprev = __shfl_up(dq, 1);
     const int jprev = __shfl_up(jq, 1);
     int rank = lane;
     if (__ballot(act && lane > 0 && (dprev > dq || (dprev == dq && jprev > jq))) != 0ull) {
         rank = 0;
-        const double dr = dq == dq ? dq : (double)INFINITY;
+        const double dr = bad ? (double)lane : dq == dq ? dq : (double)INFINITY;
         const int gb = (threadIdx.x & 63) & ~(G - 1);
         for (int p = 0; p < k; ++p) {
             const double dp = __shfl(dr, gb + p);
             const int jp = __shfl(jq, gb + p);
-            rank += (dp < dr || (dp == dr && (jp < jq || (jp == jq && p < lane)))) ? 1 : 0;
+            rank += (dp < dr || (dp == dr && jp < jq)) ? 1 : 0;
         }
         if (lane >= k) rank = lane;
     }

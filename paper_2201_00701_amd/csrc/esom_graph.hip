@@ -100,7 +100,8 @@ __global__ void __launch_bounds__(64 * GRAPH_U * GRAPH_VG) landmark_graph_kernel
             const double df = (double)Lv[q] - Lu[q];
             s = __dadd_rn(s, __dmul_rn(df, df));
         }
-        const double cd = live ? s : INFINITY;
+        // an infinite distance (no finite one reaches DBL_MAX) competes by index
+        const double cd = !live ? INFINITY : s == INFINITY ? DBL_MAX : s;
         if (__ballot(cd < bd[KC - 1]) == 0ull) continue;
         // v ascends, so a tie keeps the earlier entry first and a strict
         // comparison orders by (distance, index); every slot after the

@@ -55,3 +55,19 @@ def test_layout_hub_and_empty_entries(torch_dev, oracle_mod, g, kg, steps, room)
     # rounded to a float after every step (2^-24 of its size each), and a step
     # carries a difference on by at most a factor of the force's gradient
     assert np.abs(got - ref).max() <= steps * 4.0 * 2.0 ** -24 * max(1.0, np.abs(ref).max())
+
+
+# infinite landmarks: their distances compete by index, as in a plain FP64 evaluation
+@pytest.mark.parametrize("g,d,kg", [(5, 3, 4), (70, 17, 32), (300, 48, 10), (40, 130, 30), (33, 5, 8)])
+def test_graph_of_infinite_landmarks(torch_dev, g, d, kg):
+    from paper_2201_00701_amd import esom
+    rng = np.random.default_rng(g + d)
+    L = rng.integers(-3, 4, (g, d)).astype(np.float32)
+    L[1, 0], L[g - 2, d - 1] = np.inf, -np.inf
+    print("case graph of infinite landmarks g=%d d=%d kg=%d" % (g, d, kg), flush=True)
+    nbr, d2 = esom.landmark_graph(torch_dev.from_numpy(L).cuda(), kg)
+    D = ((L[:, None].astype(np.float64) - L[None]) ** 2).sum(2)  # whole numbers or infinite, NaN on the diagonal
+    want = np.stack([np.lexsort((np.arange(g)[np.arange(g) != u], D[u, np.arange(g) != u])) for u in range(g)])[:, :kg]
+    want = want + (want >= np.arange(g)[:, None])
+    np.testing.assert_array_equal(nbr.cpu().numpy(), want)
+    np.testing.assert_array_equal(d2.cpu().numpy(), np.take_along_axis(D, want, 1))

@@ -71,7 +71,7 @@ hipError_t launch_som_mask(const int32_t *rows, int B, int64_t n, int32_t *neare
 // Bound by the latency of the tile loads, hence TR = 4 and 32 loads of a thread
 // in flight where that tile leaves room for two blocks per CU (d <= 64).  The
 // batch's rows are gathered straight from X.  nearest[i] = -1 for an entry
-// outside [0, n) and for a point without finite distances.
+// outside [0, n) and for a NaN point.
 template <int PW, int TR>
 __global__ void __launch_bounds__(64 * SOM_WAVES) som_bmu(const float *__restrict__ X, int64_t n, int64_t ldx, int d,
                                                           const float *__restrict__ L, int g,
@@ -83,10 +83,12 @@ __global__ void __launch_bounds__(64 * SOM_WAVES) som_bmu(const float *__restric
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int i0 = (blockIdx.x * SOM_WAVES + wv) * PW;
     double *xw = xs + (size_t)wv * PW * d;
+    unsigned live = 0u;  // bit p: entry i0 + p presents a point
 #pragma unroll
     for (int p = 0; p < PW; ++p) {
         const int32_t r = i0 + p < B ? rows[i0 + p] : -1;
         const bool ok = r >= 0 && r < n;
+        live |= (ok ? 1u : 0u) << p;
         const float *xr = X + (ok ? (int64_t)r * ldx : 0);
         for (int t = lane; t < d; t += 64) xw[p * d + t] = ok ? (double)xr[t] : 0.0;
     }
@@ -157,11 +159,21 @@ __global__ void __launch_bounds__(64 * SOM_WAVES) som_bmu(const float *__restric
 #pragma unroll
     for (int p = 0; p < PW; ++p) {
         const double m = __ockl_wfred_min_f64(best[p]);
-        const int j = __ockl_wfred_min_i32(best[p] == m ? bj[p] : 0x7fffffff);
-        if (lane == 0 && i0 + p < B) {
-            const int32_t r = rows[i0 + p];
-            nearest[i0 + p] = (r >= 0 && r < n && j < g) ? j : -1;
+        int j = __ockl_wfred_min_i32(best[p] == m ? bj[p] : 0x7fffffff);
+        if (m == INFINITY) {
+            // no finite distance: the infinite ones compete by index
+            int jf = 0x7fffffff;
+            for (int v = lane; v < g && jf == 0x7fffffff; v += 64) {
+                double s = 0.0;
+                for (int q = 0; q < d; ++q) {
+                    const double df = xw[p * d + q] - (double)L[(size_t)v * d + q];
+                    s = fma(df, df, s);
+                }
+                if (s == INFINITY) jf = v;
+            }
+            j = __ockl_wfred_min_i32(jf);
         }
+        if (lane == 0 && i0 + p < B) nearest[i0 + p] = ((live >> p) & 1u) && j < g ? j : -1;
     }
 }
 

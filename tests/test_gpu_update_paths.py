@@ -105,3 +105,36 @@ def test_som_train_paths(torch_dev, oracle_mod, B, d, g):
     # one FP32 rounding a step on both sides, from FP64 values
     np.testing.assert_allclose(got, ref, rtol=T * RTOL, atol=T * RTOL * 3)
     np.testing.assert_array_equal(got[frozen == 1], L[frozen == 1])
+
+
+# an infinite batch point is equally far from all landmarks (the lowest index), a NaN
+# point has no nearest; on both sides of the direct path's largest batch
+@pytest.mark.parametrize("B", [1, 70, 4096, 4097])
+def test_som_train_non_finite_rows(torch_dev, B):
+    from paper_2201_00701_amd import esom
+    n, d, g = 64, 9, 130
+    rng = np.random.default_rng(B)
+    X = rng.integers(-3, 4, (n, d)).astype(np.float32)
+    L = rng.integers(-3, 4, (g, d)).astype(np.float32)
+    l = rng.normal(0, 2, (g, 2)).astype(np.float32)
+    X[0, 2], X[9, 2], X[11, 4] = np.inf, -np.inf, np.nan
+    rows = np.full((1, B), -1, np.int32)
+    m = min(B, n)
+    rows[0, :m] = rng.permutation(n)[:m] if B > 1 else 0
+    ctx = esom.Context(0)
+    try:
+        print("case som train non-finite rows B=%d" % B, flush=True)
+        Ld = _dev(torch_dev, L)
+        ctx.som_train(_dev(torch_dev, X), Ld, _dev(torch_dev, l), _dev(torch_dev, rows), [1.5], [0.5])
+        got = Ld.cpu().numpy()
+    finally:
+        ctx.close()
+    x = X[rows[0, :m]].astype(np.float64)
+    x = x[~np.isnan(x).any(1)]
+    near = ((x[:, None] - L[None].astype(np.float64)) ** 2).sum(2).argmin(1)
+    d2 = ((l[:, None].astype(np.float64) - l[None]) ** 2).sum(2)
+    h = np.exp(-d2 / (2.0 * 1.5 ** 2))[:, near]
+    ok = np.arange(d) != 2  # the infinite dimension spreads to every landmark
+    ref = L[:, ok] + 0.5 / B * (h @ x[:, ok] - h.sum(1)[:, None] * L[:, ok])
+    np.testing.assert_allclose(got[:, ok], ref, rtol=RTOL, atol=RTOL * 3)
+    assert not np.isfinite(got[:, 2]).any()

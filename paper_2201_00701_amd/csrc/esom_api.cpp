@@ -75,22 +75,48 @@ size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 bool aligned4(const void *p) { return ((uintptr_t)p & 3u) == 0; }
 
-int dev_alloc(esom_ctx *c, void **p, size_t bytes) {
-    if (c->budget && c->held + bytes > c->budget)
-        return fail(ESOM_ENOMEM, "scratch of %zu bytes exceeds the context budget (%zu held of %zu)",
-                    bytes, c->held, c->budget);
-    hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess) return fail(ESOM_ENOMEM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
-    c->held += bytes;
-    return ESOM_OK;
-}
-
 void dev_free(esom_ctx *c, void *&p, size_t bytes) {
     if (p) {
         (void)hipFree(p);
         c->held -= bytes;
         p = nullptr;
     }
+}
+
+// Gives back memory that no later call needs to find and that the next call to use it
+// sets up again: the 3-D pair table and the layout's workspace, and when there is
+// neither, the update's workspace.  False when there was nothing.  (A call takes its
+// own of these after all else that it allocates.)
+bool release_optional(esom_ctx *c) {
+    if (!c->k3tab && !c->lay && !c->uws) return false;
+    if (hipDeviceSynchronize() != hipSuccess) return false;
+    if (c->k3tab || c->lay) {
+        dev_free(c, reinterpret_cast<void *&>(c->k3tab), c->k3tab_bytes);
+        dev_free(c, c->lay, c->lay_bytes);
+        c->k3tab_bytes = c->lay_bytes = 0;
+    } else {
+        dev_free(c, c->uws, c->uws_bytes);
+        c->uws_bytes = 0;
+    }
+    return true;
+}
+
+// optional: the caller goes on without the memory, so nothing is given back for it.
+int dev_alloc(esom_ctx *c, void **p, size_t bytes, bool optional = false) {
+    for (;;) {
+        const bool over = c->budget && c->held + bytes > c->budget;
+        const hipError_t e = over ? hipErrorOutOfMemory : hipMalloc(p, bytes);
+        if (e == hipSuccess) break;
+        if (!over) (void)hipGetLastError();  // the launches that follow ask for theirs
+        if (!optional && release_optional(c)) continue;
+        *p = nullptr;
+        if (over)
+            return fail(ESOM_ENOMEM, "scratch of %zu bytes exceeds the context budget (%zu held of %zu)",
+                        bytes, c->held, c->budget);
+        return fail(ESOM_ENOMEM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
+    }
+    c->held += bytes;
+    return ESOM_OK;
 }
 
 }  // namespace
@@ -756,6 +782,21 @@ int grow_nearest(esom_ctx *c, int64_t n, hipStream_t s) {
     return st;
 }
 
+int grow_layout(esom_ctx *c, size_t need, bool optional, hipStream_t s) {
+    if (need <= c->lay_bytes) return ESOM_OK;
+    if (optional && c->budget && c->held - c->lay_bytes + need > c->budget)
+        return fail(ESOM_ENOMEM, "no room for %zu bytes in the context budget", need);
+    if (c->lay) {
+        hipError_t e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
+        dev_free(c, c->lay, c->lay_bytes);
+        c->lay_bytes = 0;
+    }
+    int st = dev_alloc(c, &c->lay, need, optional);
+    if (st == ESOM_OK) c->lay_bytes = need;
+    return st;
+}
+
 int grow_update_ws(esom_ctx *c, int64_t n, int g, int d, int64_t nearest_ld, hipStream_t s) {
     const size_t need = update_workspace_bytes(n, g, d, nearest_ld, c->budget != 0);
     if (need <= c->uws_bytes) return ESOM_OK;
@@ -817,7 +858,6 @@ int esom_som_train(esom_ctx *c, const float *X, int64_t n, int32_t d, int64_t ld
         c->som_xb_bytes = xb;
     }
     if ((st = grow_nearest(c, batch, s)) != ESOM_OK) return st;
-    if ((st = grow_update_ws(c, batch, g, d, 1, s)) != ESOM_OK) return st;
     esom_params P;
     esom_default_params(&P);
     P.k = 1;
@@ -832,6 +872,7 @@ int esom_som_train(esom_ctx *c, const float *X, int64_t n, int32_t d, int64_t ld
         if (st != ESOM_OK) return st;
         e = launch_som_mask(rows, batch, n, c->nearest, s);
         if (e != hipSuccess) return hip_fail(e, "batch mask launch");
+        if ((st = grow_update_ws(c, batch, g, d, 1, s)) != ESOM_OK) return st;
         UpdateArgs u;
         u.X = c->som_xb;
         u.n = batch;
@@ -973,7 +1014,7 @@ int esom_embed3(esom_ctx *c, const float *X, int64_t n, int32_t d, int64_t ldx, 
     // the k nearest landmarks (screen, exact selection, exact path)
     st = run_embed(c, X, n, d, ldx, L_hd, nullptr, g, P, nullptr, kidx, nullptr, EMBED_KNN_ONLY, s);
     if (st != ESOM_OK) return st;
-    // the FP64 pair table, where it pays and the budget has room for it
+    // the FP64 pair table, where it pays and there is room for it
     size_t tb = embed3_table_bytes(n, g, P.k);
     if (tb > c->k3tab_bytes && c->budget && c->held - c->k3tab_bytes + tb > c->budget) tb = 0;
     if (tb > c->k3tab_bytes) {
@@ -983,8 +1024,10 @@ int esom_embed3(esom_ctx *c, const float *X, int64_t n, int32_t d, int64_t ldx, 
             dev_free(c, reinterpret_cast<void *&>(c->k3tab), c->k3tab_bytes);
             c->k3tab_bytes = 0;
         }
-        st = dev_alloc(c, reinterpret_cast<void **>(&c->k3tab), tb);
-        if (st != ESOM_OK) return st;
+        if (dev_alloc(c, reinterpret_cast<void **>(&c->k3tab), tb, true) != ESOM_OK) {
+            t_err.clear();
+            tb = 0;
+        }
         c->k3tab_bytes = tb;
     }
     ListArgs a;
@@ -1055,25 +1098,15 @@ int esom_graph_layout(esom_ctx *c, const float *L_hd, int32_t g, int32_t d, cons
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // without room for the edge lists in the context's budget, the steps search
-    // the neighbour lists themselves
+    // without room for the edge lists, the steps search the neighbour lists themselves
     int edges = 1;
-    size_t need = layout_workspace_bytes(g, edges);
-    if (need > c->lay_bytes && c->budget && c->held - c->lay_bytes + need > c->budget) {
+    int st = grow_layout(c, layout_workspace_bytes(g, 1), true, s);
+    if (st == ESOM_ENOMEM) {
         edges = 0;
-        need = layout_workspace_bytes(g, edges);
+        st = grow_layout(c, layout_workspace_bytes(g, 0), false, s);
+        if (st == ESOM_OK) t_err.clear();
     }
-    if (need > c->lay_bytes) {
-        if (c->lay) {
-            e = hipStreamSynchronize(s);
-            if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-            dev_free(c, c->lay, c->lay_bytes);
-            c->lay_bytes = 0;
-        }
-        int st = dev_alloc(c, &c->lay, need);
-        if (st != ESOM_OK) return st;
-        c->lay_bytes = need;
-    }
+    if (st != ESOM_OK) return st;
     e = launch_layout(L_hd, g, d, nbr, kg, L_2d, c->lay, edges, fixed, steps, lp->scale, lp->repulsion,
                       lp->softening, lp->step, lp->max_move, s);
     if (e != hipSuccess) return hip_fail(e, "layout launch");

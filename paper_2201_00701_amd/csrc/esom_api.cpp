@@ -797,17 +797,25 @@ int grow_layout(esom_ctx *c, size_t need, bool optional, hipStream_t s) {
     return st;
 }
 
-int grow_update_ws(esom_ctx *c, int64_t n, int g, int d, int64_t nearest_ld, hipStream_t s) {
-    const size_t need = update_workspace_bytes(n, g, d, nearest_ld, c->budget != 0);
-    if (need <= c->uws_bytes) return ESOM_OK;
+// The update's workspace: as much of it as the context's budget leaves room for, or
+// the least where that is not to be had.
+int grow_update_ws(esom_ctx *c, int64_t n, int g, int d, int64_t nearest_ld, hipStream_t s, UpdatePlan &plan) {
+    const size_t room = c->budget ? c->budget - (c->held - c->uws_bytes) : SIZE_MAX;
+    plan = update_plan(n, g, d, nearest_ld, room);
+    if (plan.bytes <= c->uws_bytes) return ESOM_OK;
     if (c->uws) {
         hipError_t e = hipStreamSynchronize(s);
         if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
         dev_free(c, c->uws, c->uws_bytes);
         c->uws_bytes = 0;
     }
-    int st = dev_alloc(c, &c->uws, need);
-    if (st == ESOM_OK) c->uws_bytes = need;
+    int st = dev_alloc(c, &c->uws, plan.bytes, true);
+    if (st != ESOM_OK) {
+        plan = update_plan(n, g, d, nearest_ld, 0);
+        st = dev_alloc(c, &c->uws, plan.bytes);
+        if (st == ESOM_OK) t_err.clear();
+    }
+    if (st == ESOM_OK) c->uws_bytes = plan.bytes;
     return st;
 }
 
@@ -872,7 +880,8 @@ int esom_som_train(esom_ctx *c, const float *X, int64_t n, int32_t d, int64_t ld
         if (st != ESOM_OK) return st;
         e = launch_som_mask(rows, batch, n, c->nearest, s);
         if (e != hipSuccess) return hip_fail(e, "batch mask launch");
-        if ((st = grow_update_ws(c, batch, g, d, 1, s)) != ESOM_OK) return st;
+        UpdatePlan plan;
+        if ((st = grow_update_ws(c, batch, g, d, 1, s, plan)) != ESOM_OK) return st;
         UpdateArgs u;
         u.X = c->som_xb;
         u.n = batch;
@@ -889,7 +898,7 @@ int esom_som_train(esom_ctx *c, const float *X, int64_t n, int32_t d, int64_t ld
         u.counts = nullptr;
         u.frozen = frozen;
         u.batch = batch;
-        e = launch_update(u, c->uws, c->budget != 0, s);
+        e = launch_update(u, c->uws, plan, s);
         if (e != hipSuccess) return hip_fail(e, "online SOM update launch");
     }
     return ESOM_OK;
@@ -956,7 +965,8 @@ int esom_landmark_update(esom_ctx *c, const float *X, int64_t n, int32_t d, int6
         if (st != ESOM_OK) return st;
         near = c->nearest;
     }
-    st = grow_update_ws(c, n, g, d, near_ld, s);
+    UpdatePlan plan;
+    st = grow_update_ws(c, n, g, d, near_ld, s, plan);
     if (st != ESOM_OK) return st;
     UpdateArgs u;
     u.X = X;
@@ -972,7 +982,7 @@ int esom_landmark_update(esom_ctx *c, const float *X, int64_t n, int32_t d, int6
     u.nearest = near;
     u.nearest_ld = near_ld;
     u.counts = counts;
-    e = launch_update(u, c->uws, c->budget != 0, s);
+    e = launch_update(u, c->uws, plan, s);
     if (e != hipSuccess) return hip_fail(e, "landmark update launch");
     return ESOM_OK;
 }

@@ -197,11 +197,17 @@ struct UpdateArgs {
     const uint8_t *frozen = nullptr;  // kind 2: landmarks that keep their position
     int64_t batch = 1;                // kind 2: batch size of the averaged online step
 };
-// Workspace of an update of n points whose nearest landmarks lie nearest_ld
-// apart; tight (contexts with a memory budget): the sums and at most 4 bytes a
-// point.  launch_update takes the same `tight`.
-size_t update_workspace_bytes(int64_t n, int g, int d, int64_t nearest_ld, bool tight);
-hipError_t launch_update(const UpdateArgs &u, void *ws, bool tight, hipStream_t s);
+// How an update of n points whose nearest landmarks lie nearest_ld apart runs in a
+// workspace of at most `room` bytes: the ranges of points whose sums are kept apart,
+// and whether the nearest landmarks are copied together.  room = 0: the least, the
+// sums alone.
+struct UpdatePlan {
+    int ranges;
+    bool compact;
+    size_t bytes;
+};
+UpdatePlan update_plan(int64_t n, int g, int d, int64_t nearest_ld, size_t room);
+hipError_t launch_update(const UpdateArgs &u, void *ws, const UpdatePlan &plan, hipStream_t s);
 
 // The materialised-distance path (esom_materialise.hip): keys of a chunk of
 // points in device memory, then selection, exact rescoring and certificate.

@@ -230,49 +230,47 @@ __global__ void __launch_bounds__(UPD_BLOCK) upd_blend(const double *__restrict_
 
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// Landmark groups of a shape, and the ranges n points go in: together enough
-// blocks to fill the chip once, each range of at least ACC_RANGE points.  One
-// range needs no partial array beside the sums.  tight (contexts with a memory
-// budget): the partial arrays take no more than 4 bytes a point.
+// Landmark groups of a shape.
 static int acc_group(int g, int d) {
     const int gg = (int)(ACC_LDS_BYTES / (sizeof(double) * d + sizeof(int)));
     const int groups = (g + gg - 1) / gg;
     return (g + groups - 1) / groups;
 }
 static int acc_groups(int g, int d) { return (g + acc_group(g, d) - 1) / acc_group(g, d); }
-static int acc_ranges(int64_t n, int g, int d, bool tight) {
+
+// The ranges n points go in: with the groups enough blocks to fill the chip once,
+// each range of at least ACC_RANGE points, as many as there is room for (with the
+// sums of 3 ranges 100k points x 32-D, 400 landmarks, take 411 us, of all 98 ranges
+// 32).  One range needs no partial array beside the sums.  The compact copy comes
+// after the ranges.
+UpdatePlan update_plan(int64_t n, int g, int d, int64_t nearest_ld, size_t room) {
+    const size_t sums = sizeof(double) * (size_t)g * (d + 1);
+    UpdatePlan u;
     int64_t r = (n + ACC_RANGE - 1) / ACC_RANGE;
     if (r > ACC_BLOCKS / acc_groups(g, d)) r = ACC_BLOCKS / acc_groups(g, d);
-    if (tight) {
-        const int64_t most = (int64_t)(sizeof(int32_t) * (size_t)n / (sizeof(double) * (size_t)g * (d + 1)));
-        if (r > most) r = most;
-    }
-    return r < 1 ? 1 : (int)r;
-}
-static bool acc_compact(int g, int d, int64_t nearest_ld, bool tight) {
-    return acc_groups(g, d) > 1 && nearest_ld > 1 && !tight;
-}
-
-size_t update_workspace_bytes(int64_t n, int g, int d, int64_t nearest_ld, bool tight) {
-    const size_t sums = sizeof(double) * (size_t)g * (d + 1);
-    const int r = acc_ranges(n, g, d, tight);
-    return al256(sums) + (r > 1 ? al256(sums * r) : 0) +
-           (acc_compact(g, d, nearest_ld, tight) ? al256(sizeof(int32_t) * (size_t)(n > 0 ? n : 1)) : 0);
+    const int64_t most = room > al256(sums) + 255 ? (int64_t)((room - al256(sums) - 255) / sums) : 0;
+    if (r > most) r = most;
+    u.ranges = r < 1 ? 1 : (int)r;
+    u.bytes = al256(sums) + (u.ranges > 1 ? al256(sums * u.ranges) : 0);
+    const size_t copy = al256(sizeof(int32_t) * (size_t)(n > 0 ? n : 1));
+    u.compact = n > 0 && acc_groups(g, d) > 1 && nearest_ld > 1 && room > u.bytes && room - u.bytes >= copy;
+    if (u.compact) u.bytes += copy;
+    return u;
 }
 
-hipError_t launch_update(const UpdateArgs &u, void *ws, bool tight, hipStream_t s) {
+hipError_t launch_update(const UpdateArgs &u, void *ws, const UpdatePlan &plan, hipStream_t s) {
     const size_t sb = sizeof(double) * (size_t)u.g * (u.d + 1);
     char *p = static_cast<char *>(ws);
     double *sums = reinterpret_cast<double *>(p), *partial = sums;
     p += al256(sb);
-    const int ranges = acc_ranges(u.n, u.g, u.d, tight);
+    const int ranges = plan.ranges;
     if (ranges > 1) {
         partial = reinterpret_cast<double *>(p);
         p += al256(sb * ranges);
     }
     const int32_t *near = u.nearest;
     int64_t ld = u.nearest_ld;
-    if (u.n > 0 && acc_compact(u.g, u.d, ld, tight)) {
+    if (plan.compact) {
         int32_t *c = reinterpret_cast<int32_t *>(p);
         hipLaunchKernelGGL(upd_compact, dim3((unsigned)((u.n + 255) / 256)), dim3(256), 0, s, near, ld, u.n, c);
         near = c;

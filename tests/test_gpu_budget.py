@@ -84,3 +84,40 @@ def _given_back(data, first, needs):
 @pytest.mark.parametrize("first,needs", [("embed3", 4 * 40_000 * K), ("layout", 8 * G)])
 def test_optional_memory_is_given_back(torch_dev, data, first, needs):
     _given_back(data, first, needs)
+
+
+# the partial sums take the room there is, and give it back
+def test_update_workspace_is_given_back(torch_dev, data):
+    _given_back(data, "update", 8 * G * (D + 1))
+
+
+# the least workspace of an update (the sums alone), room for a few ranges of partial
+# sums, for all of them, and for the compact copy of a strided list
+@pytest.mark.parametrize("ranges,copy", [(0, 0), (1, 0), (3, 0), (3, 1), (300, 0), (300, 1)])
+def test_update_in_the_room_there_is(torch_dev, data, ranges, copy):
+    from paper_2201_00701_amd import esom
+    rng = np.random.default_rng(8)
+    n, d, g = 40_001, 64, 700
+    X = rng.integers(-8, 9, (n, d)).astype(np.float32)
+    L = rng.normal(0, 2, (g, d)).astype(np.float32)
+    near = rng.integers(-1, g + 1, (n, 3)).astype(np.int32)
+    al = lambda b: (b + 255) & ~255
+    sums = 8 * g * (d + 1)
+    dev = lambda a: torch_dev.from_numpy(np.ascontiguousarray(a)).cuda()
+    ctx = esom.Context(0, 128 + al(sums) + al(ranges * sums) + copy * al(4 * n) + 256)
+    try:
+        print("case update room ranges=%d copy=%d" % (ranges, copy), flush=True)
+        Ld = dev(L)
+        cnt = ctx.landmark_update(dev(X), Ld, dev(L[:, :2]), kind="kmeans", alpha=1.0, nearest=dev(near)[:, 0],
+                                  counts=True)
+        got, cnt = Ld.cpu().numpy(), cnt.cpu().numpy()
+    finally:
+        ctx.close()
+    ok = (near[:, 0] >= 0) & (near[:, 0] < g)
+    c = np.bincount(near[ok, 0], minlength=g)
+    S = np.zeros((g, d))
+    np.add.at(S, near[ok, 0], X[ok].astype(np.float64))
+    np.testing.assert_array_equal(cnt, c)
+    # whole sums are exact; one rounding of the mean, and two FP64 operations on the way
+    want = np.where(c[:, None] > 0, S / np.maximum(c, 1)[:, None], L)
+    np.testing.assert_allclose(got, want, rtol=2.0 ** -23, atol=2.0 ** -50)

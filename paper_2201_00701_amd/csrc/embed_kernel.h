@@ -1685,8 +1685,12 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                 // rows from the block's LDS copy, or by quads from memory
                 if constexpr (ROWS == 1) {
                     const float4 *Lr = reinterpret_cast<const float4 *>(rowsL + row_offset<RS>(j));
+                    // four partial sums joined as the quads join theirs, so that a
+                    // distance has the same bits wherever the rows lie
+                    float sum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int q = 0; q < DP / 4; ++q) add4(acc, x + 4 * q, Lr[q]);
+                    for (int q = 0; q < DP / 4; ++q) add4(sum[q & 3], x + 4 * q, Lr[q]);
+                    acc = (sum[0] + sum[1]) + (sum[2] + sum[3]);
                 } else {
                     const char *base = reinterpret_cast<const char *>(a.Lpad);
                     const unsigned off = mul24((unsigned)j, 4u * DP);

@@ -126,3 +126,25 @@ def test_nearest_landmark_of_non_finite_points(torch_dev):
     ok = ~np.isnan(X).any(1)
     d2 = ((X[ok][:, None].astype(np.float64) - L[None]) ** 2).sum(2)
     np.testing.assert_array_equal(cnt, np.bincount(d2.argmin(1), minlength=g))
+
+
+# shapes whose landmark rows stay in LDS for a small call, while a large one (points in
+# locality order) reads them from memory: the same bits either way
+@pytest.mark.parametrize("d,g,k", [(24, 512, 12), (16, 700, 16), (9, 600, 8)])
+@pytest.mark.parametrize("mode", ["bf16", "fp32"])
+def test_rows_in_lds_bit_identical(torch_dev, d, g, k, mode):
+    from paper_2201_00701_amd import esom
+    n = 70_001
+    rng = np.random.default_rng(d + g)
+    L = rng.normal(0, 3, (g, d)).astype(np.float32)
+    X = (L[rng.integers(0, g, n)] + rng.normal(0, 1, (n, d))).astype(np.float32)
+    Xd, Ld, ld = _dev(torch_dev, X), _dev(torch_dev, L), _dev(torch_dev, rng.normal(0, 3, (g, 2)).astype(np.float32))
+    ctx = esom.Context(0)
+    try:
+        print("case rows in LDS d=%d g=%d k=%d %s" % (d, g, k, mode), flush=True)
+        whole = [t.cpu().numpy() for t in ctx.embed(Xd, Ld, ld, k=k, mode=mode, knn=True)]
+        parts = [[t.cpu().numpy() for t in ctx.embed(p, Ld, ld, k=k, mode=mode, knn=True)] for p in Xd.split(30_000)]
+    finally:
+        ctx.close()
+    for i in range(3):
+        np.testing.assert_array_equal(whole[i], np.concatenate([p[i] for p in parts]))

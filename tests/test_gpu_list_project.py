@@ -97,3 +97,28 @@ def test_embed3_non_finite_rows(torch_dev, oracle_mod, n, d, g, k):
     np.testing.assert_array_equal(idxb[infs], np.tile(np.arange(k), (3, 1)))
     np.testing.assert_allclose(outb[infs], np.tile(l3[:k].astype(np.float64).mean(0), (3, 1)), rtol=2.0 ** -23,
                                atol=2.0 ** -23)
+
+
+# the returned list in the order of (distance, index): whole numbers with frequent exact
+# ties, and landmarks one ulp apart, which FP32 misorders; every lane group
+@pytest.mark.parametrize("ties", [True, False])
+@pytest.mark.parametrize("n,d,g,k", [(700, 6, 90, 12), (65, 9, 400, 16), (700, 6, 90, 24), (400, 17, 100, 40),
+                                     (300, 5, 64, 64)])
+def test_embed3_list_order(torch_dev, oracle_mod, n, d, g, k, ties):
+    from paper_2201_00701_amd import esom
+    rng = np.random.default_rng(n + d + k)
+    if ties:
+        X, L = rng.integers(-3, 4, (n, d)).astype(np.float32), rng.integers(-3, 4, (g, d)).astype(np.float32)
+    else:
+        X, L = rng.normal(0, 2, (n, d)).astype(np.float32), rng.normal(0, 2, (g, d)).astype(np.float32)
+        L[1::2] = L[0::2]
+        L[1::2, 3] = np.nextafter(L[0::2, 3], np.float32(9))
+    l3 = rng.normal(0, 3, (g, 3)).astype(np.float32)
+    dev = lambda a: torch_dev.from_numpy(np.ascontiguousarray(a)).cuda()
+    ctx = esom.Context(0)
+    try:
+        print("case embed3 list order n=%d d=%d g=%d k=%d ties=%s" % (n, d, g, k, ties), flush=True)
+        _, idx = ctx.embed3(dev(X), dev(L), dev(l3), k=k, knn=True)
+    finally:
+        ctx.close()
+    np.testing.assert_array_equal(idx.cpu().numpy(), oracle_mod.embed3(X, L, l3, k, threads=8)["idx"][:, :k])

@@ -1268,13 +1268,19 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
             // the low parts one tile ahead (their latency took 8K cycles a wave at
             // 1M x 32-D, where the high parts are in LDS)
             TileRegs<1, DC> Th, Tl[2];
-            load_tile<1, DC>(a.A16, 0, lane, Tl[0]);
+            // (beyond 64 dimensions it takes registers from the operands: 200k x 128-D,
+            // 400 landmarks, k = 16, 353 us ahead, 344 not)
+            constexpr bool AHEAD = DC <= 4;
+            if constexpr (AHEAD) load_tile<1, DC>(a.A16, 0, lane, Tl[0]);
             for (int tp = 0; tp < W; ++tp) {
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
                     const int t = 2 * tp + half;
                     f32x16 acc[2];
-                    load_tile<1, DC>(a.A16, t + 1 < 2 * W ? t + 1 : t, lane, Tl[1 - half]);
+                    if constexpr (AHEAD)
+                        load_tile<1, DC>(a.A16, t + 1 < 2 * W ? t + 1 : t, lane, Tl[1 - half]);
+                    else
+                        load_tile<1, DC>(a.A16, t, lane, Tl[half]);
                     load_tile<1, DC>(Ab, t, lane, Th);
                     screen_tile_split<DC>(Nb, t, lane, Th, Tl[half], P16, P16lo, acc);
                     consume(acc, half);
@@ -1450,7 +1456,12 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                     for (int c = 0; c < DC; ++c) {
                         float v[8];
                         centred8(xr, centL, a.d, c, h, valid, v);
-                        const u32x4 hw = __builtin_bit_cast(u32x4, P16.b[p][c]);
+                        // (opaque to the compiler, which would otherwise keep the first
+                        // reading's unpacked high parts and remainders through pass 1:
+                        // its tile loop then reloads 64 words a lane at 128-D)
+                        u32x4 hw = __builtin_bit_cast(u32x4, P16.b[p][c]);
+                        asm volatile("" : "+v"(hw));
+                        P16.b[p][c] = __builtin_bit_cast(bf16x8, hw);
                         u32x4 lw;
 #pragma unroll
                         for (int e = 0; e < 8; e += 2)
@@ -1705,18 +1716,26 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                     // doubled and the fused kernel took 1.010 ms at 1M x 48-D;
                     // in this order 0.790 ms, lane by lane 0.896 ms, and at 10M
                     // x 64-D 8.25 against 10.26 ms).
-                    float4 lv[DC][4];
-#pragma unroll
-                    for (int c = 0; c < DC; ++c)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            lv[c][q] = *reinterpret_cast<const float4 *>(base + (size_t)(o[q] + 64u * c));
-                    __builtin_amdgcn_sched_barrier(0);
                     float sum[4] = {0.f, 0.f, 0.f, 0.f};
+                    // chunks in flight, 16 registers each (200k x 128-D, 1024
+                    // landmarks, k = 16: all 8 at once 707 us, 4 and 4 528)
+                    constexpr int CH = DC <= 4 ? DC : 4;
 #pragma unroll
-                    for (int c = 0; c < DC; ++c)
+                    for (int c0 = 0; c0 < DC; c0 += CH) {
+                        float4 lv[CH][4];
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) add4(sum[q], x + 4 * (c + DC * q), lv[c][q]);
+                        for (int c = 0; c < CH; ++c)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                if (c0 + c < DC)
+                                    lv[c][q] = *reinterpret_cast<const float4 *>(base + (size_t)(o[q] + 64u * (c0 + c)));
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int c = 0; c < CH; ++c)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                if (c0 + c < DC) add4(sum[q], x + 4 * (c0 + c + DC * q), lv[c][q]);
+                    }
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const float t = quad_sum(sum[q]);

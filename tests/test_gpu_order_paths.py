@@ -148,3 +148,24 @@ def test_rows_in_lds_bit_identical(torch_dev, d, g, k, mode):
         ctx.close()
     for i in range(3):
         np.testing.assert_array_equal(whole[i], np.concatenate([p[i] for p in parts]))
+
+
+# BF16 mode above 64 dimensions: 5 to 8 chunks of 16, whole and ragged; landmark rows in
+# LDS and from memory
+@pytest.mark.parametrize("d", [65, 80, 96, 97, 112, 128])
+@pytest.mark.parametrize("g,k", [(70, 8), (70, 12), (600, 16), (600, 24)])
+def test_bf16_wide_rows(torch_dev, oracle_mod, d, g, k):
+    from paper_2201_00701_amd import esom
+    X, L, l = _whole(300, d, g, d + g + k)
+    ctx = esom.Context(0)
+    try:
+        print("case bf16 wide rows d=%d g=%d k=%d" % (d, g, k), flush=True)
+        out, idx, d2 = ctx.embed(_dev(torch_dev, X), _dev(torch_dev, L), _dev(torch_dev, l), k=k, mode="bf16", knn=True)
+        out, idx, d2 = out.cpu().numpy().astype(np.float64), idx.cpu().numpy(), d2.cpu().numpy()
+    finally:
+        ctx.close()
+    ref = oracle_mod.embed(X, L, l, k, threads=8)
+    np.testing.assert_array_equal(idx, ref["idx"][:, :k])
+    np.testing.assert_array_equal(d2, ref["d2"][:, :k])  # whole numbers below 2^24
+    scale = np.maximum(float(np.ptp(l, axis=0).max()), np.abs(ref["out"]).max(axis=1))
+    assert (np.abs(out - ref["out"]).max(axis=1) / scale).max() <= 1e-4

@@ -27,10 +27,14 @@ static hipError_t launch_dc(const EmbedArgs &a, int block, size_t smem, int num_
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, block, smem) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
-    // A block's waves take tiles gridDim.x apart, so that few tiles spread over as
-    // many CUs as there are (the other waves only help to stage the rows).  1024
-    // points x 16-D: 25 us in full blocks, 19 so.
-    long long blocks = (a.n + 63) / 64;
+    // A block's waves take tiles gridDim.x apart, so few tiles spread over as many CUs
+    // as there are (the other waves only help to stage the rows): 1024 points x 16-D,
+    // 25 us in full blocks, 19 so.  A CU gets further blocks only when all are full:
+    // the first waves of its blocks share a SIMD.  60k points x 48-D, 1024 landmarks,
+    // FP32 mode (4-wave blocks): a call takes 221 us with a tile for every resident
+    // block first, 183 so.
+    const long long tiles = (a.n + 63) / 64, full = (tiles * 64 + block - 1) / block;
+    long long blocks = full >= num_cus ? full : tiles < num_cus ? tiles : num_cus;
     if (blocks > (long long)per_cu * num_cus) blocks = (long long)per_cu * num_cus;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(block), smem, s, a);

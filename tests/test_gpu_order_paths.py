@@ -169,3 +169,25 @@ def test_bf16_wide_rows(torch_dev, oracle_mod, d, g, k):
     np.testing.assert_array_equal(d2, ref["d2"][:, :k])  # whole numbers below 2^24
     scale = np.maximum(float(np.ptp(l, axis=0).max()), np.abs(ref["out"]).max(axis=1))
     assert (np.abs(out - ref["out"]).max(axis=1) / scale).max() <= 1e-4
+
+
+# few tiles for the blocks: one less and one more than a CU each, and than the waves of a
+# block on every CU (256 CUs, 4-wave blocks), rows from memory; a point's result follows
+# from the point alone
+@pytest.mark.parametrize("n", [1, 255 * 64, 256 * 64 + 1, 1023 * 64 + 5, 1024 * 64 - 1])
+def test_few_tiles(torch_dev, n):
+    from paper_2201_00701_amd import esom
+    d, g, k = 20, 1000, 16
+    rng = np.random.default_rng(9)
+    L = rng.normal(0, 3, (g, d)).astype(np.float32)
+    X = (L[rng.integers(0, g, n)] + rng.normal(0, 1, (n, d))).astype(np.float32)
+    Xd, Ld, ld = _dev(torch_dev, X), _dev(torch_dev, L), _dev(torch_dev, rng.normal(0, 3, (g, 2)).astype(np.float32))
+    ctx = esom.Context(0)
+    try:
+        print("case few tiles n=%d" % n, flush=True)
+        whole = [t.cpu().numpy() for t in ctx.embed(Xd, Ld, ld, k=k, mode="fp32", knn=True)]
+        parts = [[t.cpu().numpy() for t in ctx.embed(p, Ld, ld, k=k, mode="fp32", knn=True)] for p in Xd.split(4096)]
+    finally:
+        ctx.close()
+    for i in range(3):
+        np.testing.assert_array_equal(whole[i], np.concatenate([p[i] for p in parts]))

@@ -375,6 +375,18 @@ __device__ __forceinline__ float quad_sum(float v) {
     v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xf, 0xf, true));  // lanes 2 3 0 1
     return v;
 }
+template <int CTRL>
+__device__ __forceinline__ double dpp64(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double quad_sum64(double v) {
+    v += dpp64<0xB1>(v);
+    v += dpp64<0x4E>(v);
+    return v;
+}
 
 // The value of lane U of the calling lane's row of 16 lanes.
 template <int U>
@@ -1048,12 +1060,14 @@ __global__ void __launch_bounds__(256) embed_project(EmbedArgs a) {
         const float *xr = a.X + (valid ? pi : 0) * a.ldx;
         auto d2x = [&](int jl) -> double {
             const float *Lr = a.Lpad + (size_t)iposL[jl] * a.dp;
-            double acc = 0.0;
-            for (int t = 0; t < a.d; ++t) {
-                const double e = (double)xr[t] - (double)Lr[t];
-                acc = fma(e, e, acc);
-            }
-            return acc;
+            double sum[4] = {0.0, 0.0, 0.0, 0.0};  // as the fused kernel sums
+            for (int t0 = 0; t0 < a.d; t0 += 16)
+#pragma unroll
+                for (int t = 0; t < 16; ++t) {
+                    const double e = t0 + t < a.d ? (double)xr[t0 + t] - (double)Lr[t0 + t] : 0.0;
+                    sum[t / 4] = fma(e, e, sum[t / 4]);
+                }
+            return (sum[0] + sum[1]) + (sum[2] + sum[3]);
         };
         float cref[N_REFINE] = {};
         int nref = 0;
@@ -1794,45 +1808,69 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
         int nref = 0;
         if constexpr (KP <= 8 && KP > 1) {
             if (!a.knn_only) {
-                // rows of more than 64 dimensions, or held by quads, are read
-                // again from memory
+                // the walk's sums in FP64: four parts, joined as the quads join theirs.
+                // Rows of more than 64 dimensions are read again from memory, lane by
+                // lane (held until here they cost registers).  Below, quads read them
+                // as in the walk: lane by lane, 200k uniform points x 64-D, 1024
+                // landmarks, k = 8 took 404 us a call, now 332.
                 const float *xr = a.X + (valid ? pi : 0) * a.ldx;
                 auto d2x = [&](int jl) -> double {
                     const unsigned pos = iposL[jl];
-                    const float4 *Lr = ROWS ? reinterpret_cast<const float4 *>(rowsL + row_offset<RS>(pos))
-                                                  : reinterpret_cast<const float4 *>(a.Lpad + (size_t)pos * DP);
-                    double acc = 0.0;
-                    auto add4 = [&](float4 xv, float4 lv) {
-                        const double e0 = (double)xv.x - (double)lv.x;
-                        const double e1 = (double)xv.y - (double)lv.y;
-                        const double e2 = (double)xv.z - (double)lv.z;
-                        const double e3 = (double)xv.w - (double)lv.w;
+                    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+                    auto add4 = [](double &acc, const float *xv, const float4 lv) {
+                        const double e0 = (double)xv[0] - (double)lv.x, e1 = (double)xv[1] - (double)lv.y;
+                        const double e2 = (double)xv[2] - (double)lv.z, e3 = (double)xv[3] - (double)lv.w;
                         acc = fma(e0, e0, acc);
                         acc = fma(e1, e1, acc);
                         acc = fma(e2, e2, acc);
                         acc = fma(e3, e3, acc);
                     };
-                    if constexpr (DC <= 4 && ROWS == 1) {
+                    if constexpr (ROWS == 0 && DC <= 4) {
+                        const char *base = reinterpret_cast<const char *>(a.Lpad);
+                        const int off = (int)mul24(pos, 4u * DP);
+                        const unsigned lo16 = 16u * (lane & 3);
+                        const unsigned o[4] = {(unsigned)quad_bcast<0>(off) + lo16, (unsigned)quad_bcast<1>(off) + lo16,
+                                               (unsigned)quad_bcast<2>(off) + lo16, (unsigned)quad_bcast<3>(off) + lo16};
 #pragma unroll
-                        for (int q = 0; q < DP / 4; ++q)
-                            add4(make_float4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]), Lr[q]);
+                        for (int c = 0; c < DC; ++c) {
+                            float4 lv[4];
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                lv[q] = *reinterpret_cast<const float4 *>(base + (size_t)(o[q] + 64u * c));
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) add4(sum[q], x + 4 * (c + DC * q), lv[q]);
+                        }
+                        double own = 0.0;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const double t = quad_sum64(sum[q]);
+                            own = (lane & 3) == q ? t : own;
+                        }
+                        return own;
+                    }
+                    const float4 *Lr = ROWS ? reinterpret_cast<const float4 *>(rowsL + row_offset<RS>(pos))
+                                            : reinterpret_cast<const float4 *>(a.Lpad + (size_t)pos * DP);
+                    if constexpr (DC <= 4) {
+#pragma unroll
+                        for (int q = 0; q < DP / 4; ++q) add4(sum[q & 3], x + 4 * q, Lr[q]);
                     } else {
 #pragma unroll 4
                         for (int q = 0; q < DP / 4; ++q) {
-                            float4 xv;
+                            float xv[4];
                             if (4 * q + 4 <= a.d) {
                                 const Float4U u = reinterpret_cast<const Float4U *>(xr)[q];
-                                xv = make_float4(u.x, u.y, u.z, u.w);
+                                xv[0] = u.x;
+                                xv[1] = u.y;
+                                xv[2] = u.z;
+                                xv[3] = u.w;
                             } else {
-                                xv.x = 4 * q < a.d ? xr[4 * q] : 0.f;
-                                xv.y = 4 * q + 1 < a.d ? xr[4 * q + 1] : 0.f;
-                                xv.z = 4 * q + 2 < a.d ? xr[4 * q + 2] : 0.f;
-                                xv.w = 0.f;
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) xv[e] = 4 * q + e < a.d ? xr[4 * q + e] : 0.f;
                             }
-                            add4(xv, Lr[q]);
+                            add4(sum[q & 3], xv, Lr[q]);
                         }
                     }
-                    return acc;
+                    return (sum[0] + sum[1]) + (sum[2] + sum[3]);
                 };
                 reason |= refine_cutoffs<KP>(a, sk, valid, d2x, cref, nref);
             }

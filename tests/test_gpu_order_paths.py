@@ -191,3 +191,29 @@ def test_few_tiles(torch_dev, n):
         ctx.close()
     for i in range(3):
         np.testing.assert_array_equal(whole[i], np.concatenate([p[i] for p in parts]))
+
+
+# small cutoff weights (k up to 8) from FP64 distances: many of them (distances nearly
+# alike), landmark rows in LDS and from memory, below and above 64 dimensions, against
+# the oracle; and the same bits in a large call
+@pytest.mark.parametrize("d,g,k,mode", [(17, 520, 8, "bf16"), (16, 700, 5, "fp32"), (40, 520, 8, "bf16"),
+                                        (64, 600, 7, "fp32"), (65, 520, 8, "bf16"), (112, 90, 8, "bf16")])
+def test_small_cutoff_weights(torch_dev, oracle_mod, d, g, k, mode):
+    from paper_2201_00701_amd import esom
+    n, m = 66_000, 1500
+    rng = np.random.default_rng(d + g + k)
+    L, X = rng.random((g, d), dtype=np.float32), rng.random((n, d), dtype=np.float32)
+    l = rng.normal(0, 3, (g, 2)).astype(np.float32)
+    Xd, Ld, ld = _dev(torch_dev, X), _dev(torch_dev, L), _dev(torch_dev, l)
+    ctx = esom.Context(0)
+    try:
+        print("case small cutoff weights d=%d g=%d k=%d %s" % (d, g, k, mode), flush=True)
+        out = ctx.embed(Xd, Ld, ld, k=k, mode=mode).cpu().numpy()
+        part = ctx.embed(Xd[:m], Ld, ld, k=k, mode=mode).cpu().numpy()
+    finally:
+        ctx.close()
+    np.testing.assert_array_equal(out[:m], part)
+    ref = oracle_mod.embed(X[:m], L, l, k, threads=8)["out"]
+    # the library's coordinate bar: 1e-4 of the grid span, or of an output beyond it
+    scale = np.maximum(float(np.ptp(l, axis=0).max()), np.abs(ref).max(axis=1))
+    assert (np.abs(part - ref).max(axis=1) / scale).max() <= 1e-4

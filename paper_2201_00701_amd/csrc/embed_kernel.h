@@ -1618,7 +1618,7 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
         const bool valid = pbase + lane < a.n;
         const int64_t pi = valid ? slot_point<ROWS>(a, pbase + lane) : 0;  // the point's own index
         const float cert_rhs = certL[lane];
-        // The point's row.  ROWS = 1: in the lane's registers.  ROWS = 0 (landmark
+        // The point's row.  ROWS = 1: in the lane's registers.  By quads (landmark
         // rows from memory): the four lanes of a quad rescore one candidate at a
         // time together, each on every fourth float4 of the rows, so x holds this
         // lane's pieces of its quad's four points: [4 c + 4 DC s ...] the
@@ -1626,8 +1626,13 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
         // load then covers 16 rows with 64 consecutive bytes each instead of 64
         // rows with 16: the kernel was bound by the L1's line accesses (0.92 a
         // clock at 1M x 48-D with 1024 landmarks, half of them the walk's).
+        // Up to 16 dimensions a row is one line, and with the long lists (KP > 24)
+        // the quads' moves cost more than they save: 200k points x 8-D, 600
+        // landmarks, k = 28, 421 us by quads, 415 lane by lane; but 400k x 16-D, 1024
+        // landmarks, k = 16, 250 and 255.
         float x[DP];
-        if constexpr (ROWS == 1) {
+        constexpr bool QUADS = ROWS == 0 && (DC > 1 || KP <= 24);
+        if constexpr (!QUADS) {
             const float *xr = a.X + (valid ? pi : 0) * a.ldx;
 #pragma unroll
             for (int t = 0; t < DP / 4; ++t) {
@@ -1708,8 +1713,9 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                     sum = fmaf(e3, e3, sum);
                 };
                 // rows from the block's LDS copy, or by quads from memory
-                if constexpr (ROWS == 1) {
-                    const float4 *Lr = reinterpret_cast<const float4 *>(rowsL + row_offset<RS>(j));
+                if constexpr (!QUADS) {
+                    const float4 *Lr = ROWS ? reinterpret_cast<const float4 *>(rowsL + row_offset<RS>(j))
+                                            : reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(a.Lpad) + row_offset<4 * DP>(j));
                     // four partial sums joined as the quads join theirs, so that a
                     // distance has the same bits wherever the rows lie
                     float sum[4] = {0.f, 0.f, 0.f, 0.f};
@@ -1825,7 +1831,7 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                         acc = fma(e2, e2, acc);
                         acc = fma(e3, e3, acc);
                     };
-                    if constexpr (ROWS == 0 && DC <= 4) {
+                    if constexpr (QUADS && DC <= 4) {
                         const char *base = reinterpret_cast<const char *>(a.Lpad);
                         const int off = (int)mul24(pos, 4u * DP);
                         const unsigned lo16 = 16u * (lane & 3);

@@ -217,3 +217,25 @@ def test_small_cutoff_weights(torch_dev, oracle_mod, d, g, k, mode):
     # the library's coordinate bar: 1e-4 of the grid span, or of an output beyond it
     scale = np.maximum(float(np.ptp(l, axis=0).max()), np.abs(ref).max(axis=1))
     assert (np.abs(part - ref).max(axis=1) / scale).max() <= 1e-4
+
+
+# lists past 24 with rows of at most 16 dimensions from memory (read lane by lane), and
+# one chunk more (by quads); large calls in locality order and small ones
+@pytest.mark.parametrize("d,g,k,mode", [(5, 600, 25, "bf16"), (16, 520, 32, "fp32"), (8, 100, 30, "fp32"),
+                                        (17, 600, 30, "bf16")])
+def test_long_lists_short_rows(torch_dev, oracle_mod, d, g, k, mode):
+    from paper_2201_00701_amd import esom
+    n, m = 66_000, 700
+    X, L, l = _whole(n, d, g, d + g + k)
+    Xd, Ld, ld = _dev(torch_dev, X), _dev(torch_dev, L), _dev(torch_dev, l)
+    ctx = esom.Context(0)
+    try:
+        print("case long lists short rows d=%d g=%d k=%d %s" % (d, g, k, mode), flush=True)
+        _, idx, d2 = [t.cpu().numpy() for t in ctx.embed(Xd, Ld, ld, k=k, mode=mode, knn=True)]
+        _, idxm, d2m = [t.cpu().numpy() for t in ctx.embed(Xd[:m], Ld, ld, k=k, mode=mode, knn=True)]
+    finally:
+        ctx.close()
+    ref = oracle_mod.embed(X[:m], L, l, k, threads=8)
+    for i, e in ((idx[:m], d2[:m]), (idxm, d2m)):
+        np.testing.assert_array_equal(i, ref["idx"][:, :k])
+        np.testing.assert_array_equal(e, ref["d2"][:, :k])  # whole numbers below 2^24

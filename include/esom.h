@@ -93,7 +93,8 @@ typedef struct {
     int64_t n_fallback;    /* points recomputed by the exact FP64 path */
     int64_t n_uncertified; /* ...because the screen certificate failed */
     int64_t n_near_tie;    /* ...because the k-th and (k+1)-th distances are
-                              closer than FP32 can order */
+                              closer than FP32 can order, or, where the neighbour
+                              list is returned, two entries of it are */
     int64_t n_illcond;     /* ...because the 2x2 system is ill-conditioned or a
                               landmark pair is nearly duplicate */
     int64_t n_degenerate;  /* ...because all k distances are equal or all scores
@@ -106,7 +107,8 @@ typedef struct {
     double ms_prep;        /* summed device time of landmark preparation (and of
                               the points' locality order where it outlasts it) */
     double ms_main;        /* summed device time of the fused embed kernel */
-    double ms_exact;       /* summed device time of the exact FP64 path */
+    double ms_exact;       /* summed device time of the exact FP64 path, with the
+                              ranking of lists that are open in their order alone */
 } esom_stats;
 
 /* Fills *p with the defaults (k = 16, boost 1, adjust 1, cutoff 10,
@@ -114,7 +116,12 @@ typedef struct {
 void esom_default_params(esom_params *p);
 
 /* Creates a context on HIP device `device`.  hbm_budget_bytes bounds the
- * device memory the context may hold (0 = no bound besides the device).
+ * device memory the context may hold (0 = no bound besides the device).  Memory
+ * that only makes a call faster (the 3-D pair table, the layout's edge lists, the
+ * update's partial sums) is taken as the bound leaves room, and given back, after
+ * a wait for the device, to a call that would otherwise be refused.  A graph
+ * captured from calls on a context refers to its memory: replay it only until a
+ * call needs more than those before it.
  * The context owns one extra HIP stream (default priority) and two events:
  * for 512 or more landmarks and 65536 or more points, esom_embed orders the
  * points for locality on that stream while the landmark preparation runs on
@@ -136,8 +143,8 @@ const char *esom_last_error(void);
  *   out      device, n x 2 floats (written)
  *   knn_idx  device, n x k int32 or NULL: the k nearest landmark indices, sorted
  *            by (exact distance, index): entries closer than FP32 rescoring can
- *            order are ranked again in FP64; -1 for a point without k finite
- *            distances (non-finite input), whose output is then NaN
+ *            order are ranked again in FP64 (infinite distances by index); -1 for
+ *            a point with fewer than k distances other than NaN, whose output is NaN
  *   knn_dist2 device, n x k floats or NULL: their squared distances (FP32)
  * n == 0 is a no-op.  Errors: ESOM_EINVAL for k < 3, k > g, k > ESOM_MAX_K,
  * d < 1 or > ESOM_MAX_D, g > ESOM_MAX_G, n < 0, ldx < d, NULL or misaligned
@@ -253,7 +260,8 @@ int esom_fit_landmarks(const float *L_hd, const float *L_2d, int32_t g, int32_t 
  * nearest landmarks are found exactly as by esom_embed (same screen, exact
  * selection and exact path); scores and pairs are then evaluated in FP64.
  *   L_3d     device, g x 3 floats
- *   out      device, n x 3 floats (written; NaN for a point without k finite distances)
+ *   out      device, n x 3 floats (written; NaN for a point with fewer than k distances
+ *            other than NaN)
  *   knn_idx  device, n x k int32 or NULL: the k nearest, as esom_embed returns them
  * Other arguments, limits and errors as for esom_embed. */
 int esom_embed3(esom_ctx *ctx, const float *X, int64_t n, int32_t d, int64_t ldx, const float *L_hd,
@@ -299,10 +307,11 @@ void esom_default_layout_params(esom_layout_params *p);
 /* Runs `steps` layout steps on L_2d (device, g x 2 floats, 8-byte aligned,
  * updated in place).  nbr: the graph (device, g x kg int32; -1 entries are
  * ignored).  fixed: device, g bytes or NULL; nodes with fixed[u] != 0 keep
- * their position (dragged by the user).  The context provides a g x 2 buffer
- * for the steps.  Errors: ESOM_EINVAL for shapes as esom_landmark_graph,
+ * their position (dragged by the user).  The context provides a second g x 2
+ * buffer for the steps and, where there is room, the nodes' edge lists (about 1 KB
+ * a landmark).  Errors: ESOM_EINVAL for shapes as esom_landmark_graph,
  * steps < 0, parameters not finite or negative (softening <= 0), NULL or
- * misaligned arrays; ESOM_ENOMEM for the buffer beyond the context budget. */
+ * misaligned arrays; ESOM_ENOMEM for the second buffer beyond the context budget. */
 int esom_graph_layout(esom_ctx *ctx, const float *L_hd, int32_t g, int32_t d, const int32_t *nbr,
                       int32_t kg, float *L_2d, const uint8_t *fixed, int32_t steps,
                       const esom_layout_params *params, void *stream);

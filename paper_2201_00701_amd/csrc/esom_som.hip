@@ -60,11 +60,11 @@ hipError_t launch_som_mask(const int32_t *rows, int B, int64_t n, int32_t *neare
 //   som_blend  L_j += (alpha / batch) sum_i h(j, b_i) (x_i - L_j) straight from
 //              the batch's rows.
 // The general path (gather, landmark preparation, MFMA screen, exact path, mask,
-// counting sort, sums, blend: 13 launches) is for larger batches: its screen
-// costs less per point, but its launches and the preparation take about 100 us a
-// step however small the batch.  400 landmarks, 32-D, batch 1024: 397 us a step
-// by the general path with a blend that formed its weights per dimension (about
-// 120 us with upd_blend), now 30 us.
+// sums, blend: ten or eleven launches) is for larger batches: its screen costs less
+// per point, but its launches and the preparation take most of the 69 us of a step of
+// 5000 points (400 landmarks, 32-D).  Batch 1024: 397 us a step by that path as it
+// was, with a counting sort and a blend that formed its weights per dimension, now
+// 30 us.
 
 // One wavefront per PW points; the block's wavefronts share landmark tiles of
 // 64 TR rows in LDS (odd row stride: no bank conflicts), lane = TR landmarks.

@@ -20,21 +20,24 @@
 namespace esom {
 
 template <int MODE, int DC, int KP>
-static hipError_t launch_dc(const EmbedArgs &a, int block, size_t smem, int num_cus, hipStream_t s) {
+static hipError_t launch_dc(const EmbedArgs &a0, int block, size_t smem, int num_cus, hipStream_t s) {
     constexpr int KF = INST_KF;
+    EmbedArgs a = a0;
+    a.cus = num_cus;
     auto kern = a.lds_rows ? embed_main<MODE, DC, KP, 1, KF> : embed_main<MODE, DC, KP, 0, KF>;
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, block, smem) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
-    // A block's waves take tiles gridDim.x apart, so few tiles spread over as many CUs
-    // as there are (the other waves only help to stage the rows): 1024 points x 16-D,
-    // 25 us in full blocks, 19 so.  A CU gets further blocks only when all are full:
-    // the first waves of its blocks share a SIMD.  60k points x 48-D, 1024 landmarks,
-    // FP32 mode (4-wave blocks): a call takes 221 us with a tile for every resident
-    // block first, 183 so.
-    const long long tiles = (a.n + 63) / 64, full = (tiles * 64 + block - 1) / block;
-    long long blocks = full >= num_cus ? full : tiles < num_cus ? tiles : num_cus;
+    // A block's waves take tiles gridDim.x apart.  Up to a tile for every CU, a block
+    // each (the other waves only help to stage the rows): 1024 points x 16-D, 25 us in
+    // full blocks, 19 so.  Up to a tile for every wave of one block a CU, that block:
+    // its waves go through the operand together (60k points x 32-D, 1024 landmarks,
+    // FP32 mode, 150 us a call, 161 on three blocks a CU).  Beyond, all blocks that are
+    // resident, and few tiles over them evenly (70k x 75-D, 661 landmarks, k = 24, 218
+    // us; in full blocks, 17 CUs with two, 252).
+    const long long tiles = (a.n + 63) / 64;
+    long long blocks = tiles > (long long)num_cus * (block / 64) || tiles < num_cus ? tiles : num_cus;
     if (blocks > (long long)per_cu * num_cus) blocks = (long long)per_cu * num_cus;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(block), smem, s, a);

@@ -119,6 +119,7 @@ struct EmbedArgs {
     int knn_only;  // 1: only write knn outputs (no projection)
     int lds_rows;  // 1: the block stages Lpad in LDS (row stride dp + 4 floats)
     int lds_tiles; // 1: the block stages the screen operands (A tiles, norms) in LDS
+    int cus;       // CUs of the device
     // Optional per-point mark beside knn outputs (serving cache): 1 when the
     // point's neighbours came from the exact path because of the screen
     // (uncertified or near tie); a projection from cached neighbours sends

@@ -1730,8 +1730,20 @@ __global__ void __launch_bounds__(main_max_block(MODE, DC, KP)) embed_main(Embed
                     // four partial sums joined as the quads join theirs, so that a
                     // distance has the same bits wherever the rows lie
                     float sum[4] = {0.f, 0.f, 0.f, 0.f};
+                    // (Four reads in flight: left to itself the compiler issues and
+                    // awaits them one by one here; 20k points x 64-D, 400 landmarks, k =
+                    // 16, 92 us a call, 86 so, and no less with eight.  Beyond 64
+                    // dimensions it takes registers from the row: 200k x 128-D, 100
+                    // landmarks, k = 24, 585 us so, 332 without.)
 #pragma unroll
-                    for (int q = 0; q < DP / 4; ++q) add4(sum[q & 3], x + 4 * q, Lr[q]);
+                    for (int c = 0; c < DC; ++c) {
+                        float4 lv[4];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) lv[q] = Lr[4 * c + q];
+                        if constexpr (DC <= 4) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) add4(sum[q], x + 4 * (4 * c + q), lv[q]);
+                    }
                     acc = (sum[0] + sum[1]) + (sum[2] + sum[3]);
                 } else {
                     const char *base = reinterpret_cast<const char *>(a.Lpad);
